@@ -54,7 +54,7 @@ MALL_ROTATE_BYTES = 512 << 20
 CALIB_TOKENS = 128
 PROFILES = os.path.join(ROOT, "profiles")
 # sources whose change invalidates a stored traffic measurement of the VMM kernel
-VMM_SOURCES = ("paper_2606_23419_amd/csrc/vmm_pp.hip", "paper_2606_23419_amd/csrc/vmm_dot2.hip",
+VMM_SOURCES = ("paper_2606_23419_amd/csrc/vmm_mm.hip", "paper_2606_23419_amd/csrc/vmm_pp.hip", "paper_2606_23419_amd/csrc/vmm_dot2.hip",
                "paper_2606_23419_amd/csrc/vmm_common.h", "paper_2606_23419_amd/csrc/vmm.hip",
                "paper_2606_23419_amd/csrc/grinqh_internal.h")
 

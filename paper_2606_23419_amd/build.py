@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libgrinqh.so")
 SOURCES = ["grinqh_api.hip", "pack.hip", "assign.hip", "vmm.hip", "vmm_dot2.hip", "vmm_pp.hip",
-           "prefill.hip", "vmm_lut.hip"]
+           "vmm_mm.hip",           "prefill.hip", "vmm_lut.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -21,13 +21,15 @@ HIPCC_FLAGS = [
 ]
 
 
-# per-source extra flags: prefill.hip keeps its fixed-size register arrays in
-# registers (the compiler would otherwise place some in LDS, which its
-# double-buffered tiles need); vmm_pp.hip preloads its first kernel arguments
+# per-source extra flags: prefill.hip and vmm_mm.hip keep their fixed-size register
+# arrays in registers (the compiler would otherwise place some in LDS, which
+# their tiles need); vmm_pp.hip and vmm_mm.hip preload their first kernel arguments
 SOURCE_FLAGS = {"prefill.hip": ["-mllvm", "-disable-promote-alloca-to-lds"],
                 # the batch-1 kernels' leading arguments (x, level map, groups)
                 # arrive in scalar registers at wave launch, so the first load
                 # of x does not wait for a kernel-argument load
+                "vmm_mm.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=16",
+                               "-mllvm", "-disable-promote-alloca-to-lds"],
                 "vmm_pp.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=16"]}
 
 

@@ -100,9 +100,14 @@ int launch_calibrate(const Layer& L, const void* x, int S, const QuantilePos& qp
 constexpr int kCalibScratch = 1 << 17;   // 1 MiB
 int launch_calibrate_noalloc(const Layer& L, const void* x, int S, const QuantilePos& qp,
                              float* theta, hipStream_t s);
+// B = 1..4 tokens; levels from the level map, or graded in the kernel from
+// thresholds (th) or, at B = 1 and 2-bit planes, the exact top-k cuts of x
+// (tk), then optionally written to level_map_out
+int launch_vmm_mm(const Layer& L, const void* codes, const void* scales, const void* x,
+                  const uint8_t* level_map, const Thresholds* th, const TopkCuts* tk,
+                  uint8_t* level_map_out, int B, float* y, hipStream_t s);
 bool vmm_pp_supported(const Layer& L, int B);
-// levels from the level map, or graded in the kernel from thresholds (th) or
-// the exact top-k cuts of x (tk), then optionally written to level_map_out
+bool vmm_pp_takes(const Layer& L, int B);
 int launch_vmm_pp(const Layer& L, const void* codes, const void* scales, const void* x,
                   const uint8_t* level_map, const Thresholds* th, const TopkCuts* tk,
                   uint8_t* level_map_out, float* y, hipStream_t s);

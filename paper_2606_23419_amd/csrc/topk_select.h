@@ -1,5 +1,5 @@
 // Exact top-k cuts of one token's |x| (App. A.1 top-p partition), computed
-// by the 256 threads of a VMM workgroup in its prologue, so that the top-k
+// by the 256 or 512 threads of a VMM workgroup in its prologue, so that the top-k
 // mode needs no separate assignment launch.  Every workgroup of a launch
 // computes the same cuts from the whole x.
 //
@@ -9,12 +9,12 @@
 // key q_k is in cut j iff (q_k << 16) + 65535 - k >= cut[j], and a channel's
 // level is the number of cuts it is in.  C_j = 0 gives 0xFFFFFFFF (nobody).
 //
-//   1. Each thread owns a contiguous run of KP keys (KP = ceil(K / 256)
+//   1. Each thread owns a contiguous run of KP keys (KP = ceil(K / threads)
 //      rounded up to 8), so thread order is channel order; each pass below
 //      re-reads the run from x (L2-resident after the first pass), which
 //      measured faster than holding the run in registers.
 //   2. A 256-bin histogram of q >> 7 (LDS atomics); wave w scans it from the
-//      top for cuts w, w + 4: the coarse bin holding the C_j-th largest key.
+//      top for cuts w, w + waves, ..: the coarse bin holding the C_j-th largest key.
 //   3. A 128-bin histogram of q & 127 over the keys of each cut's coarse bin
 //      gives the exact key ck_j, the keys above it and those equal to it;
 //      need_j = C_j - above of the keys equal to ck_j are in.
@@ -30,7 +30,7 @@ namespace grinqh {
 namespace topksel {
 
 constexpr int kCutsMax = kMaxLevels - 1;
-constexpr int kThreads = 256;
+constexpr int kWavesMax = 8;
 constexpr int kMaxK = 16384;   // channel indices fit the low 16 bits of a composite
 static_assert(kMaxK <= 65536, "a composite holds 65535 - k in 16 bits");
 
@@ -40,7 +40,7 @@ struct Scratch {
   uint32_t binmask[256];               // bit j: coarse bin of cut j
   uint32_t bin[kCutsMax], above[kCutsMax], ck[kCutsMax], need[kCutsMax];
   uint32_t tie;                        // bit j: cut j needs the channel-order scan
-  uint32_t wtot[kCutsMax][4];          // per-wave totals of the tie counts, a row per cut
+  uint32_t wtot[kCutsMax][kWavesMax];     // per-wave totals of the tie counts, a row per cut
   uint32_t cut[kCutsMax];
 };
 
@@ -81,8 +81,11 @@ __device__ __forceinline__ uint32_t key_at(const uint4& v, int i) {
 
 // Leaves the cuts in S.cut; ends with a workgroup barrier.  x: the token's
 // fp16 x [K], K a multiple of 128 and at most kMaxK, 16-byte aligned.
+template <int kThreads>
 __device__ __forceinline__ void select_cuts(const uint16_t* __restrict__ x, int K, const TopkCuts& tk,
                                             Scratch& S) {
+  constexpr int kWaves = kThreads / 64;
+  static_assert(kWaves <= kWavesMax && kThreads >= 256, "threads");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = tk.n;
@@ -90,8 +93,10 @@ __device__ __forceinline__ void select_cuts(const uint16_t* __restrict__ x, int 
   const int kb = tid * KP;                                       // this thread's first channel
   const int words = KP >> 3;
 
-  S.hist1[tid] = 0u;
-  S.binmask[tid] = 0u;
+  if (tid < 256) {
+    S.hist1[tid] = 0u;
+    S.binmask[tid] = 0u;
+  }
   for (int i = tid; i < kCutsMax * 128; i += kThreads) (&S.hist2[0][0])[i] = 0u;
   if (tid == 0) S.tie = 0u;
   __syncthreads();
@@ -106,7 +111,7 @@ __device__ __forceinline__ void select_cuts(const uint16_t* __restrict__ x, int 
   __syncthreads();
 
   // coarse bins, from the top: lane l holds bins 255 - 4l .. 252 - 4l
-  for (int j = wave; j < n; j += 4) {
+  for (int j = wave; j < n; j += kWaves) {
     const uint32_t C = (uint32_t)tk.cum[j];
     if (!C) continue;
     const uint4 h4 = *(const uint4*)&S.hist1[252 - 4 * lane];   // bins 252-4l .. 255-4l
@@ -153,7 +158,7 @@ __device__ __forceinline__ void select_cuts(const uint16_t* __restrict__ x, int 
   __syncthreads();
 
   // exact keys: lane l holds fine bins 127 - 2l and 126 - 2l
-  for (int j = wave; j < n; j += 4) {
+  for (int j = wave; j < n; j += kWaves) {
     const uint32_t C = (uint32_t)tk.cum[j];
     if (!C) {
       if (lane == 0) S.cut[j] = 0xFFFFFFFFu;

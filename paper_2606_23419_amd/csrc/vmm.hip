@@ -155,8 +155,10 @@ int launch_vmm(const Layer& L, const void* codes, const void* scales, const void
   }
   const int force = option(&Options::vmm_kernel);   // tests and measurements
   const bool want_dot2 = force == GRINQH_KERNEL_PER_PLANE, want_v0 = force == GRINQH_KERNEL_GENERAL;
-  if (!want_dot2 && !want_v0 && vmm_pp_supported(L, B))
+  if (!want_dot2 && !want_v0 && vmm_pp_takes(L, B))
     return launch_vmm_pp(L, codes, scales, x, level_map, th, nullptr, level_map_out, y, s);
+  if (!want_dot2 && !want_v0)
+    return launch_vmm_mm(L, codes, scales, x, level_map, th, nullptr, level_map_out, B, y, s);
   if (!want_v0 && vmm_dot2_supported(L))
     return launch_vmm_dot2(L, codes, scales, x, level_map, th, level_map_out, B, y, s);
   // about 512 workgroups per token over the whole chip
@@ -186,7 +188,9 @@ int launch_vmm_topk(const Layer& L, const void* codes, const void* scales, const
     int st = check_launch("vmm zero-fill");
     if (st) return st;
   }
-  return launch_vmm_pp(L, codes, scales, x, nullptr, nullptr, &cuts, level_map_out, y, s);
+  if (vmm_pp_takes(L, 1))
+    return launch_vmm_pp(L, codes, scales, x, nullptr, nullptr, &cuts, level_map_out, y, s);
+  return launch_vmm_mm(L, codes, scales, x, nullptr, nullptr, &cuts, level_map_out, 1, y, s);
 }
 
 }  // namespace grinqh

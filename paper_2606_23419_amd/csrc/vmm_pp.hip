@@ -2,9 +2,10 @@
 // reconstruction with the midpoint bias; App. C.1 sparse bit-loading), laid
 // out for CDNA4.
 //
-// Each wave grades its own 32 rows of every group of its workgroup and sorts
+// A workgroup takes two groups.  Each wave grades 32 rows of both and sorts
 // them, with two ballots, into "big" rows (3 or 4 planes to read) and "small"
-// rows (1 or 2).  A batch gives each lane group either two big rows, planes
+// rows (1 or 2); the four waves' rows of a group form one list (big rows, then
+// small, in wave order) and the waves take its batches in turn.  A batch gives each lane group either two big rows, planes
 // 1-4 of each, or four small rows, planes 1-2 of each: eight plane dwords per
 // lane either way.  The plane a row may lack (plane 4 of a 3-plane row,
 // plane 2 of a 1-plane row) is read from an offset outside the tile's buffer
@@ -107,252 +108,6 @@ __device__ __forceinline__ float double_offset_factor(int e) {
 }
 
 template <int LPR, int D, bool TOPK>
-__global__ __launch_bounds__(256) void k_vmm_sr(
-    const uint16_t* __restrict__ x, const uint8_t* __restrict__ lm, int gw, int groups, int fused,
-    const uint8_t* __restrict__ codes, const uint16_t* __restrict__ scales, float* __restrict__ y,
-    Layer L, Thresholds th, TopkCuts tk, uint8_t* __restrict__ lm_out) {
-  constexpr int T = LPR * 16;            // outputs of the tile
-  constexpr int PLANE = T / 4;           // bytes of one plane row
-  constexpr int NLG = 64 / LPR;          // lane groups per wave
-  constexpr int kWaves = 4;
-  constexpr int MAXG = 2;                // groups per workgroup at most; gw is 1 or 2
-  constexpr int BR = 2 * NLG;            // big rows per batch of a wave
-  constexpr int SR = 4 * NLG;            // small rows per batch of a wave
-  constexpr int MB = 32 / BR + 2;        // batches per (wave, group) at most
-  // fp16 exponent bits of a merged pair's field at p = 0: 31 - 2j for the
-  // pair of planes (j, j+1); 27 for empty entries (any finite value)
-  constexpr uint32_t kE12 = 29u << 10, kE34 = 25u << 10, kEmpty = 27u << 10;
-
-  // lists: per (wave, group, batch, lane group) four entries as three
-  // 4-dword fields: offsets of plane j, of plane j+1, and (x | exponent << 16)
-  __shared__ __align__(16) uint32_t s_ent[kWaves][MAXG][MB][NLG][3][4];
-  __shared__ __align__(16) uint32_t s_empty[kWaves][3][4];
-  __shared__ __align__(16) float s_red[kWaves][T];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int half = lane >> 5, hl = lane & 31;
-  const int t = blockIdx.x;
-  const int g0 = blockIdx.y * gw;
-  const int ng = min(gw, groups - g0);
-  // loads first: x and the level map of this lane's row (lanes 0-31 the
-  // first group, 32-63 the second).  They need no field of L, so they go
-  // out before the wave waits for the layer's scalars (x, lm, gw, groups and
-  // fused lead the argument list and arrive preloaded in scalar registers)
-  const int gg = half;
-  const bool valid = gg < ng;
-  const int k = (g0 + min(gg, ng - 1)) * kGroup + 32 * wave + hl;
-  const uint32_t xv = x[k];
-  const uint32_t lv = (fused ? (const uint8_t*)x : lm)[k];   // ignored when graded here
-  const int lg = lane / LPR, li = lane % LPR;
-  const int n_top = L.n_levels - 1;
-  const __amdgpu_buffer_rsrc_t rsrc = tile_rsrc(codes + (size_t)t * L.K * L.RB, L);
-  const uint32_t li4 = (uint32_t)li * 4u;
-
-  // the scales of this lane's 16 outputs for both groups (a group past the
-  // last reads the last one again, from cache)
-  uint4 scw[MAXG][2];
-#pragma unroll
-  for (int g = 0; g < MAXG; ++g) {
-    const uint16_t* sp = scales + (size_t)(g0 + min(g, ng - 1)) * L.N + (size_t)t * T + li * 16;
-    scw[g][0] = *(const uint4*)sp;
-    scw[g][1] = *(const uint4*)(sp + 8);
-  }
-  if (lane < 12) (&s_empty[wave][0][0])[lane] = lane < 8 ? kNoRow : (kEmpty << 16);
-
-  // top-k mode: the token's cuts from the whole x, the same in every workgroup
-  // (top-k kernels only: the others hold no selection scratch)
-  __shared__ __align__(16) uint8_t s_tk_raw[TOPK ? sizeof(topksel::Scratch) : 16];
-  topksel::Scratch& s_tk = *reinterpret_cast<topksel::Scratch*>(s_tk_raw);
-  if constexpr (TOPK) topksel::select_cuts(x, L.K, tk, s_tk);
-
-  // ---- grade, sort into big and small rows, write this wave's lists
-  const float fx = h2f((uint16_t)xv);
-  const float ax = fabsf(fx);
-  int graded = 0;
-#pragma unroll
-  for (int j = 0; j < kMaxLevels - 1; ++j) graded += ax >= th.theta[j] ? 1 : 0;
-  const int lvl = min(fused == 1 ? graded
-                      : TOPK ? topksel::level_of(xv, k, tk.n, s_tk)
-                                   : (int)(lv & 0xFFu),
-                      n_top);
-  if (fused && lm_out && t == 0 && valid) lm_out[k] = (uint8_t)lvl;
-  const int d = valid ? level_planes(L.planes_packed, lvl) : 0;
-  const bool big = d >= 3, small = d == 1 || d == 2;
-  const int nbig = half_total(big), nsm = half_total(small);
-  const int rank = big ? half_below(big) : half_below(small);
-  const int nbb = (nbig + BR - 1) / BR, nsb = (nsm + SR - 1) / SR;
-  const float bs = half_sum_dpp(d ? fx * phi_minus_offset(2 * d, L.bmax) : 0.0f);
-  {
-    uint32_t* E = &s_ent[wave][gg][0][0][0][0];
-    const uint32_t base = (uint32_t)k * (uint32_t)L.RB;
-    const uint32_t xh = xv & 0xFFFFu;
-    auto put = [&](int b, int lgp, int s, uint32_t o1, uint32_t o2, uint32_t xe) {
-      uint32_t* p = E + (b * NLG + lgp) * 12 + s;
-      p[0] = o1;
-      p[4] = o2;
-      p[8] = xe;
-    };
-    if (valid && big) {
-      const int b = rank / BR, w = rank % BR;
-      put(b, w >> 1, w & 1, base, base + PLANE, xh | (kE12 << 16));
-      put(b, w >> 1, (w & 1) + 2, base + 2 * PLANE, d >= 4 ? base + 3 * PLANE : kNoRow, xh | (kE34 << 16));
-    }
-    if (valid && small) {
-      const int b = nbb + rank / SR, w = rank % SR;
-      put(b, w >> 2, w & 3, base, d >= 2 ? base + PLANE : kNoRow, xh | (kE12 << 16));
-    }
-    // empty entries up to whole batches: no memory access, zero coefficient
-    if (valid) {
-      for (int r = nbig + hl; r < nbb * BR; r += 32) {
-        const int b = r / BR, w = r % BR;
-        put(b, w >> 1, w & 1, kNoRow, kNoRow, kEmpty << 16);
-        put(b, w >> 1, (w & 1) + 2, kNoRow, kNoRow, kEmpty << 16);
-      }
-      for (int r = nsm + hl; r < nsb * SR; r += 32) {
-        const int b = nbb + r / SR, w = r % SR;
-        put(b, w >> 2, w & 3, kNoRow, kNoRow, kEmpty << 16);
-      }
-    }
-  }
-  const int nb_v = valid ? nbb + nsb : 0;
-  const int nbb_v = valid ? nbb : 0;
-  int nb_g[MAXG];
-  float beta_g[MAXG];
-  nb_g[0] = __builtin_amdgcn_readlane(nb_v, 0);
-  nb_g[1] = __builtin_amdgcn_readlane(nb_v, 32);
-  const int nbb0 = __builtin_amdgcn_readlane(nbb_v, 0), nbb1 = __builtin_amdgcn_readlane(nbb_v, 32);
-  beta_g[0] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, bs), 0));
-  beta_g[1] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, bs), 32));
-  // the lists and the empty batch are this wave's own: its LDS accesses
-  // complete in order, so keeping the compiler from moving the reads above
-  // the writes is enough
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-
-  // ---- main loop over this wave's (group, batch) sequence: D register sets,
-  // D-1 batches in flight while one is consumed
-  float yp[16], acc[16], off = 0.0f, off8 = 0.0f;
-#pragma unroll
-  for (int e = 0; e < 16; ++e) yp[e] = acc[e] = 0.0f;
-
-  struct Batch {
-    uint32_t w[8];
-    uint32_t xe[4];
-  };
-  const int bstart1 = nb_g[0], nbt = nb_g[0] + nb_g[1];
-  auto fetch = [&](Batch& B, int b) {
-    const int g = b >= bstart1 ? 1 : 0;
-    const int lb = b - (g ? bstart1 : 0);
-    const uint32_t* src = b < nbt ? &s_ent[wave][g][lb][lg][0][0] : &s_empty[wave][0][0];
-    const uint4 o1 = *(const uint4*)src;
-    const uint4 o2 = *(const uint4*)(src + 4);
-    const uint4 xe = *(const uint4*)(src + 8);
-    B.xe[0] = xe.x;
-    B.xe[1] = xe.y;
-    B.xe[2] = xe.z;
-    B.xe[3] = xe.w;
-    B.w[0] = load_plane(rsrc, o1.x + li4);
-    B.w[1] = load_plane(rsrc, o2.x + li4);
-    B.w[2] = load_plane(rsrc, o1.y + li4);
-    B.w[3] = load_plane(rsrc, o2.y + li4);
-    B.w[4] = load_plane(rsrc, o1.z + li4);
-    B.w[5] = load_plane(rsrc, o2.z + li4);
-    B.w[6] = load_plane(rsrc, o1.w + li4);
-    B.w[7] = load_plane(rsrc, o2.w + li4);
-  };
-  auto consume_big = [&](const Batch& B) {
-    const uint32_t xp = __builtin_amdgcn_perm(B.xe[1], B.xe[0], 0x05040100u);
-    off8 = dot2r(0x64006400u, xp, off8);
-    consume_quad(B.w, xp, acc);
-  };
-  auto consume = [&](const Batch& B) {
-    // (x_k1, x_k2) from the entries' low halves, the exponent bits from the high halves
-    const uint32_t xpa = __builtin_amdgcn_perm(B.xe[1], B.xe[0], 0x05040100u);
-    const uint32_t m0a = __builtin_amdgcn_perm(B.xe[1], B.xe[0], 0x07060302u);
-    const uint32_t xpb = __builtin_amdgcn_perm(B.xe[3], B.xe[2], 0x05040100u);
-    const uint32_t m0b = __builtin_amdgcn_perm(B.xe[3], B.xe[2], 0x07060302u);
-    off = dot2r(m0a, xpa, off);
-    off = dot2r(m0b, xpb, off);
-    consume_double(B.w[0], B.w[1], B.w[2], B.w[3], m0a, xpa, acc);
-    consume_double(B.w[4], B.w[5], B.w[6], B.w[7], m0b, xpb, acc);
-  };
-  // the group being consumed, the end of its big batches and of all its
-  // batches (a group without batches has no rows to add and is skipped)
-  int cur_g = nb_g[0] > 0 ? 0 : 1;
-  int cur_bigend = cur_g == 0 ? nbb0 : bstart1 + nbb1;
-  int next_fin = cur_g == 0 ? bstart1 : nbt;
-  auto finish_group = [&]() {
-    float sc[16];
-    const bool g1 = cur_g != 0;
-    const uint32_t ww[8] = {g1 ? scw[1][0].x : scw[0][0].x, g1 ? scw[1][0].y : scw[0][0].y,
-                            g1 ? scw[1][0].z : scw[0][0].z, g1 ? scw[1][0].w : scw[0][0].w,
-                            g1 ? scw[1][1].x : scw[0][1].x, g1 ? scw[1][1].y : scw[0][1].y,
-                            g1 ? scw[1][1].z : scw[0][1].z, g1 ? scw[1][1].w : scw[0][1].w};
-#pragma unroll
-    for (int h = 0; h < 8; ++h) {
-      sc[2 * h] = h2f((uint16_t)(ww[h] & 0xFFFFu));
-      sc[2 * h + 1] = h2f((uint16_t)(ww[h] >> 16));
-    }
-    const float beta = lg == 0 ? (g1 ? beta_g[1] : beta_g[0]) : 0.0f;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      yp[e] = fmaf(sc[e], acc[e] - double_offset_factor(e) * off - off8 + beta, yp[e]);
-      acc[e] = 0.0f;
-    }
-    off = 0.0f;
-    off8 = 0.0f;
-    cur_g = 1;
-    cur_bigend = bstart1 + nbb1;
-    next_fin = nbt;
-  };
-
-  // the first batches in order (a scheduler free to reorder them issues
-  // batch 0 last, and its consume then waits for all of them)
-  Batch R[D];
-#pragma unroll
-  for (int i = 0; i < D - 1; ++i) {
-    fetch(R[i], i);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  for (int b = 0; b < nbt; b += D) {
-#pragma unroll
-    for (int i = 0; i < D; ++i) {
-      fetch(R[(i + D - 1) % D], b + i + D - 1);
-      __builtin_amdgcn_sched_barrier(0);   // the loads go out before the consume waits
-      // a guard, not an exit: an early exit out of the unrolled body makes
-      // the loop header wait for every load in flight
-      if (b + i < nbt) {
-        if (b + i < cur_bigend) consume_big(R[i]);
-        else consume(R[i]);
-        if (b + i + 1 == next_fin) finish_group();
-      }
-    }
-  }
-
-  // ---- reduce: lane groups of a wave by lane swaps, waves through LDS, then
-  // one atomic add per output
-#pragma unroll
-  for (int e = 0; e < 16; ++e) yp[e] = lane_group_sum<LPR>(yp[e]);
-  if (lane < LPR) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-      *(float4*)&s_red[wave][li * 16 + 4 * c] = make_float4(yp[4 * c], yp[4 * c + 1], yp[4 * c + 2], yp[4 * c + 3]);
-  }
-  __syncthreads();
-  for (int o = tid; o < T; o += 256) {
-    const float v = s_red[0][o] + s_red[1][o] + s_red[2][o] + s_red[3][o];
-    atomicAdd(&y[(size_t)t * T + o], v * L.sfac);   // 8-bit code units -> b_max units
-  }
-}
-
-// The same VMM with the lists of a workgroup shared: the four waves' rows of
-// a group form one list (big rows, then small, in wave order) and the waves
-// take its batches in turn (wave w: batches w, w + 4, ...).  That evens the
-// waves' work and pads each list once per group rather than once per wave,
-// for two workgroup barriers in the prologue; it pays on launches of two
-// groups per workgroup, where each wave otherwise pads four lists.
-template <int LPR, int D, bool TOPK>
 __global__ __launch_bounds__(256) void k_vmm_sg(
     const uint16_t* __restrict__ x, const uint8_t* __restrict__ lm, int gw, int groups, int fused,
     const uint8_t* __restrict__ codes, const uint16_t* __restrict__ scales, float* __restrict__ y,
@@ -412,7 +167,7 @@ __global__ __launch_bounds__(256) void k_vmm_sg(
   // (top-k kernels only: the others hold no selection scratch)
   __shared__ __align__(16) uint8_t s_tk_raw[TOPK ? sizeof(topksel::Scratch) : 16];
   topksel::Scratch& s_tk = *reinterpret_cast<topksel::Scratch*>(s_tk_raw);
-  if constexpr (TOPK) topksel::select_cuts(x, L.K, tk, s_tk);
+  if constexpr (TOPK) topksel::select_cuts<256>(x, L.K, tk, s_tk);
 
   // ---- grade, sort into big and small rows
   const float fx = h2f((uint16_t)xv);
@@ -421,9 +176,7 @@ __global__ __launch_bounds__(256) void k_vmm_sg(
 #pragma unroll
   for (int j = 0; j < kMaxLevels - 1; ++j) graded += ax >= th.theta[j] ? 1 : 0;
   const int lvl = min(fused == 1 ? graded
-                      : TOPK ? topksel::level_of(xv, k, tk.n, s_tk)
-                                   : (int)(lv & 0xFFu),
-                      n_top);
+                      : TOPK ? topksel::level_of(xv, k, tk.n, s_tk) : (int)(lv & 0xFFu), n_top);
   if (fused && lm_out && t == 0 && valid) lm_out[k] = (uint8_t)lvl;
   const int d = valid ? level_planes(L.planes_packed, lvl) : 0;
   const bool big = d >= 3, small = d == 1 || d == 2;
@@ -625,28 +378,16 @@ __global__ __launch_bounds__(256) void k_vmm_sg(
 }
 
 template <int LPR>
-void launch_sr(int gw, hipStream_t s, const void* codes, const void* scales, const void* x,
+void launch_sg(int gw, hipStream_t s, const void* codes, const void* scales, const void* x,
                const uint8_t* lm, float* y, const Layer& L, int fused, const Thresholds& th,
                const TopkCuts& tk, uint8_t* lm_out) {
   const dim3 grid((unsigned)L.tiles, (unsigned)((L.groups + gw - 1) / gw));
-  // top-k selection is its own instantiation: the other kernels carry no
-  // selection code or scratch
-  if (gw == 2 && fused == 2)
-    hipLaunchKernelGGL((k_vmm_sg<LPR, 4, true>), grid, dim3(256), 0, s,
-                       (const uint16_t*)x, lm, gw, L.groups, fused, (const uint8_t*)codes,
-                       (const uint16_t*)scales, y, L, th, tk, lm_out);
-  else if (gw == 2)
-    hipLaunchKernelGGL((k_vmm_sg<LPR, 4, false>), grid, dim3(256), 0, s,
-                       (const uint16_t*)x, lm, gw, L.groups, fused, (const uint8_t*)codes,
-                       (const uint16_t*)scales, y, L, th, tk, lm_out);
-  else if (fused == 2)
-    hipLaunchKernelGGL((k_vmm_sr<LPR, 4, true>), grid, dim3(256), 0, s,
-                       (const uint16_t*)x, lm, gw, L.groups, fused, (const uint8_t*)codes,
-                       (const uint16_t*)scales, y, L, th, tk, lm_out);
+  if (fused == 2)
+    hipLaunchKernelGGL((k_vmm_sg<LPR, 4, true>), grid, dim3(256), 0, s, (const uint16_t*)x, lm, gw, L.groups,
+                       fused, (const uint8_t*)codes, (const uint16_t*)scales, y, L, th, tk, lm_out);
   else
-    hipLaunchKernelGGL((k_vmm_sr<LPR, 4, false>), grid, dim3(256), 0, s,
-                       (const uint16_t*)x, lm, gw, L.groups, fused, (const uint8_t*)codes,
-                       (const uint16_t*)scales, y, L, th, tk, lm_out);
+    hipLaunchKernelGGL((k_vmm_sg<LPR, 4, false>), grid, dim3(256), 0, s, (const uint16_t*)x, lm, gw, L.groups,
+                       fused, (const uint8_t*)codes, (const uint16_t*)scales, y, L, th, tk, lm_out);
 }
 
 }  // namespace
@@ -657,22 +398,31 @@ bool vmm_pp_supported(const Layer& L, int B) {
          (long long)L.K * L.RB < (1ll << 31);
 }
 
+// The layers this kernel takes at batch 1: from 768 (tile, group) units on
+// (merged gate|up 4096 -> 28672: 896), two groups per workgroup.  There it
+// streams 256-byte plane rows and adds half as many partial sums; against it
+// k_vmm_mm took 15.9 against 15.6 us at 4 bits and 26.1 against 22.8 at 8
+// (11.3 against 12.2 at 2 bits, which the launcher can't tell).  Below, k_vmm_mm:
+// down 14336 -> 4096 (448 units) 9.6 against 10.2 us at 4 bits, 13.6 against 13.6
+// at 8, qkv 4096 -> 6144 (384) 6.0 against 7.7.
+bool vmm_pp_takes(const Layer& L, int B) {
+  if (!vmm_pp_supported(L, B)) return false;
+  if (const int v = option(&Options::groups_per_wg)) return v >= 2;
+  return (long)L.tiles * L.groups >= 768;
+}
+
 int launch_vmm_pp(const Layer& L, const void* codes, const void* scales, const void* x,
                   const uint8_t* level_map, const Thresholds* th, const TopkCuts* tk,
                   uint8_t* level_map_out, float* y, hipStream_t s) {
-  // groups per workgroup: about 512 workgroups, rounded to the nearest count
-  // (896 (tile, group) units -> 2, 448 -> 1)
-  int gw = (int)(((long)L.tiles * L.groups + 256) / 512);
-  if (const int v = option(&Options::groups_per_wg)) gw = v;
-  gw = gw < 1 ? 1 : (gw > 2 ? 2 : gw);
+  constexpr int gw = 2;   // groups per workgroup
   Thresholds none{};
   TopkCuts nocuts{};
   const Thresholds& tt = th ? *th : none;
   const TopkCuts& cc = tk ? *tk : nocuts;
   const int fused = th ? 1 : (tk ? 2 : 0);   // levels graded here: thresholds, top-k
-  if (L.T == 256) launch_sr<16>(gw, s, codes, scales, x, level_map, y, L, fused, tt, cc, level_map_out);
-  else if (L.T == 512) launch_sr<32>(gw, s, codes, scales, x, level_map, y, L, fused, tt, cc, level_map_out);
-  else launch_sr<64>(gw, s, codes, scales, x, level_map, y, L, fused, tt, cc, level_map_out);
+  if (L.T == 256) launch_sg<16>(gw, s, codes, scales, x, level_map, y, L, fused, tt, cc, level_map_out);
+  else if (L.T == 512) launch_sg<32>(gw, s, codes, scales, x, level_map, y, L, fused, tt, cc, level_map_out);
+  else launch_sg<64>(gw, s, codes, scales, x, level_map, y, L, fused, tt, cc, level_map_out);
   return check_launch("vmm (sorted rows)");
 }
 

@@ -1,0 +1,95 @@
+"""The matrix-core decode VMM at the edges of its lists, passes and columns."""
+import numpy as np
+import pytest
+
+from oracle import grinqh_oracle as orc
+from synth import inputs
+from test_gpu_parity import Layer, _dev, _host, g, opts, torch  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def _maps(kind, B, K, top, seed):
+    r = np.random.default_rng(seed)
+    lm = np.zeros((B, K), np.uint8)
+    if kind == "full":                        # every row to full depth: a second pass
+        lm[:] = top
+    elif kind == "uneven":                    # one list of 32 channels full, its neighbours empty
+        lm[:, 32:64] = top
+        lm[:, 128 + 96:128 + 128] = top
+    elif kind == "one":                       # a single row
+        lm[:, K - 1] = 1
+    elif kind == "random":                    # every depth, tokens of their own
+        lm[:] = r.integers(0, top + 1, size=(B, K))
+    return lm
+
+
+def _bound(L, x, lm, u):
+    """Per output: X is rounded to 2^-25 of a power of two at most twice the
+    group's largest active |x| (2^-24 for 1-bit planes), each channel's code
+    is at most 255 (8-bit units), and a group's sum takes fewer than 16 float32
+    roundings, plus one per group in the adds."""
+    G = L.K // 128
+    xa = np.abs(x.astype(np.float64)) * (lm > 0)
+    xa = xa.reshape(-1, G, 128)
+    per = (lm.reshape(-1, G, 128) > 0).sum(2) * xa.max(2) * (2 if u == 1 else 1) + (16 + G) * xa.sum(2)
+    s = L.scales.astype(np.float64) * 2.0 ** (L.b_max - 8)
+    return 2.0 ** -24 * 255 * per @ s
+
+
+@pytest.mark.parametrize("kind", ["full", "uneven", "one", "empty", "random"])
+@pytest.mark.parametrize("K,N,levels,tile_n,B", [
+    (256, 256, (0, 2, 4, 8), 256, 1), (256, 1024, (0, 2, 4, 6, 8), 512, 4),
+    (384, 1024, (0, 2, 4, 6, 8), 1024, 2), (256, 2048, (0, 2, 4, 6), 2048, 3),
+    (256, 512, (0, 2, 4), 256, 4), (256, 1536, (0, 2, 4), 512, 1),
+    (256, 1024, (0, 2, 3, 4, 8), 512, 1), (256, 1024, (0, 2, 3, 4, 8), 1024, 4),
+    (256, 1024, (0, 1, 2, 3, 4), 512, 3), (256, 2048, (0, 1, 3, 6), 2048, 2)])
+def test_vmm_mm_lists(g, torch, kind, K, N, levels, tile_n, B):  # noqa: F811
+    L = Layer(g, torch, K, N, levels, cfg=90, tile_n=tile_n, codes_src=True)
+    x = inputs.activations_t3(K, B, 90)
+    lm = _maps(kind, B, K, len(levels) - 1, 90)
+    y = g.grinqh_vmm(L.desc, L.pc, L.ps, _dev(torch, x), _dev(torch, lm))
+    ref = orc.vmm_batch(L.codes, L.scales, x, lm, levels)
+    err = np.abs(_host(y) - ref)
+    assert np.all(err <= _bound(L, x, lm, L.desc.plane_bits)), (err.max(), np.abs(ref).max())
+
+
+def test_vmm_mm_columns_per_workgroup(g, torch):  # noqa: F811
+    # 2 x 896 columns of 256 outputs and one group: 2 and 3 columns per workgroup,
+    # the last workgroup with fewer
+    for N in (2 * 896 * 256, 1537 * 256):
+        K, levels = 128, (0, 2, 4, 8)
+        L = Layer(g, torch, K, N, levels, cfg=91, tile_n=256, codes_src=True)
+        g.grinqh_set_option(g.GRINQH_OPT_GROUPS_PER_WG, 1)
+        try:
+            x = inputs.activations_t3(K, 1, 91)
+            lm = _maps("random", 1, K, 3, 91)
+            y = g.grinqh_vmm(L.desc, L.pc, L.ps, _dev(torch, x), _dev(torch, lm))
+        finally:
+            g.grinqh_set_option(g.GRINQH_OPT_GROUPS_PER_WG, 0)
+        ref = orc.vmm_batch(L.codes, L.scales, x, lm, levels)
+        assert np.all(np.abs(_host(y) - ref) <= _bound(L, x, lm, 2))
+
+
+@pytest.mark.parametrize("levels,B", [((0, 2, 4, 6, 8), 1), ((0, 2, 4, 6, 8), 3), ((0, 2, 3, 4, 8), 2)])
+def test_vmm_mm_skipped_and_non_finite(g, torch, levels, B):  # noqa: F811
+    # a skipped channel leaves no trace, however large or non-finite its x; an
+    # active infinity or NaN reaches every output of its token and no other
+    K, N = 256, 1024
+    L = Layer(g, torch, K, N, levels, cfg=92, codes_src=True)
+    x = (inputs.activations_t3(K, B, 92) * np.float16(1e-3)).astype(np.float16)
+    lm = _maps("random", B, K, len(levels) - 1, 92)
+    lm[:, [5, 70, 200]] = 0
+    lm[:, 9] = 2
+    ref = orc.vmm_batch(L.codes, L.scales, np.where(lm > 0, x, 0).astype(np.float16), lm, levels)
+    bound = _bound(L, x, lm, L.desc.plane_bits)
+    big = x.copy()
+    big[:, 5], big[:, 70], big[:, 200] = 60000.0, np.inf, np.nan
+    y = _host(g.grinqh_vmm(L.desc, L.pc, L.ps, _dev(torch, big), _dev(torch, lm)))
+    assert np.all(np.abs(y - ref) <= bound)
+    for v in (np.inf, -np.inf, np.nan):
+        bad = big.copy()
+        bad[0, 9] = v
+        y = _host(g.grinqh_vmm(L.desc, L.pc, L.ps, _dev(torch, bad), _dev(torch, lm)))
+        assert not np.isfinite(y[0]).any()
+        assert np.all(np.abs(y[1:] - ref[1:]) <= bound[1:])
