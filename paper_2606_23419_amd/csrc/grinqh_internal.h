@@ -124,6 +124,9 @@ int launch_vmm(const Layer& L, const void* codes, const void* scales, const void
                int B, float* y, int accumulate, hipStream_t s);
 int launch_prefill(const Layer& L, const void* codes, const void* scales, const void* x, int M,
                    float* y, int accumulate, hipStream_t s);
+bool prefill_small_takes(const Layer& L, int M);
+int launch_prefill_small(const Layer& L, const void* codes, const void* scales, const void* x, int M,
+                         float* y, int accumulate, hipStream_t s);
 int lut_desc(const Layer& L, LutDesc* D);
 int launch_stream_read(const void* src, size_t bytes, uint32_t* sink, hipStream_t s);
 // level_map == nullptr with th != nullptr: levels graded from x in the kernel,

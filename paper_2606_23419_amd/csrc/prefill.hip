@@ -388,6 +388,8 @@ int device_cus() {
 // CU count the rounds are counted in (tests); 0 takes the device's.
 int launch_prefill(const Layer& L, const void* codes, const void* scales, const void* x, int M,
                    float* y, int accumulate, hipStream_t s) {
+  if (!option(&Options::prefill_tile) && prefill_small_takes(L, M))
+    return launch_prefill_small(L, codes, scales, x, M, y, accumulate, s);
   const long mb256 = (M + 255) / 256;
   int cfg = mb256 * (L.N / 256) >= 160 ? 0 : mb256 * (L.N / 128) >= 160 ? 1 : 2;
   int n_split = 0;   // columns of the 256 x 256 part when split

@@ -1,0 +1,59 @@
+"""Prefill of short prompts: blocks of tokens, turns, columns and K splits."""
+import numpy as np
+import pytest
+
+from oracle import grinqh_oracle as orc
+from synth import inputs
+from test_gpu_parity import Layer, _dev, _host, g, torch  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def _bound(L, x, sums):
+    """(2^-11 + K 2^-24) sum |x| |w_hat| per element, the stated contract."""
+    return (2.0 ** -11 + L.K * 2.0 ** -24) * sums
+
+
+def _sums(L, x):
+    half = 1 << (L.b_max - 1)
+    w = np.abs(L.codes.astype(np.float64) - half) * np.repeat(L.scales.astype(np.float64).T, 128, axis=1)
+    return np.abs(x.astype(np.float64)) @ w.T
+
+
+# K = 128: two turns for eight waves; N = 256 .. 8448: K split in two (up to 128
+# workgroups), one workgroup per 64 outputs, two columns per workgroup (over 256,
+# 16640 outputs); M around the 16-token tiles and the 80-token blocks
+@pytest.mark.parametrize("K,N,levels,tile_n,Ms", [
+    (128, 256, (0, 2, 4, 8), 256, (1, 16, 17, 80, 81)),
+    (1152, 1024, (0, 2, 4, 6, 8), 1024, (5, 33, 48, 161)),
+    (640, 512, (0, 2, 4, 6), 512, (2, 64, 77)),
+    (256, 2048, (0, 2, 4), 2048, (15, 96)),
+    (384, 1024, (0, 2, 3, 4, 8), 512, (1, 31, 80, 130)),
+    (256, 1024, (0, 1, 4), 1024, (49,)),
+    (256, 8448, (0, 2, 4, 8), 256, (3, 78)),
+    (256, 16640, (0, 2, 4, 8), 256, (18, 79)),
+    (256, 16896, (0, 2, 3, 4, 8), 512, (40,))])
+def test_prefill_small(g, torch, K, N, levels, tile_n, Ms):  # noqa: F811
+    L = Layer(g, torch, K, N, levels, cfg=96, tile_n=tile_n, codes_src=True)
+    for M in Ms:
+        x = inputs.activations_t3(K, M, 96)
+        xd = _dev(torch, x)
+        y = g.grinqh_prefill(L.desc, L.pc, L.ps, xd)
+        ref = orc.prefill(L.codes, L.scales, x, b_max=L.b_max)
+        bound = _bound(L, x, _sums(L, x))
+        assert np.all(np.abs(_host(y) - ref) <= bound), M
+        # bit for bit again, over whatever y held; added to y on request
+        y2 = torch.full_like(y, 3.5)
+        for _ in range(3):
+            g.grinqh_prefill(L.desc, L.pc, L.ps, xd, y=y2)
+            assert torch.equal(y, y2), M
+        g.grinqh_prefill(L.desc, L.pc, L.ps, xd, y=y2, accumulate=True)
+        assert np.all(np.abs(_host(y2) - 2 * ref) <= 2.1 * bound), M
+
+
+def test_prefill_small_rows_past_m_are_not_written(g, torch):  # noqa: F811
+    L = Layer(g, torch, 256, 512, (0, 2, 4, 8), cfg=97, codes_src=True)
+    M = 19
+    buf = torch.full((M + 13, 512), 7.0, device="cuda")
+    g.grinqh_prefill(L.desc, L.pc, L.ps, _dev(torch, inputs.activations_t3(256, M, 97)), y=buf[:M])
+    assert bool((buf[M:] == 7.0).all())
