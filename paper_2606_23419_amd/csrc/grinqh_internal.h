@@ -87,6 +87,9 @@ int option(int Options::*field);
 int fail(int status, const char* fmt, ...);
 int check_launch(const char* what);
 
+// Compute units of the current device (prefill.hip).
+int device_cus();
+
 // Kernel launchers (defined next to their kernels).
 int launch_pack(const Layer& L, int src_kind, const void* src, const void* src_scales,
                 void* packed_codes, void* packed_scales, hipStream_t s);

@@ -360,6 +360,8 @@ void launch_u(int cfg, const Layer& L, const void* codes, const void* scales, co
   else launch_cfg<U, 2, 2, 4, 2>(L, codes, scales, x, M, y, accumulate, s, n_begin, n_cols);
 }
 
+}  // namespace
+
 // Compute units of the current device (cached per device).
 int device_cus() {
   static int cus[64];
@@ -372,8 +374,6 @@ int device_cus() {
   }
   return cus[dev];
 }
-
-}  // namespace
 
 // Tile choice: 256 x 256 while that gives at least ~0.6 workgroups per CU
 // (one resident per CU), else 256 x 128 on the same condition, else 128 x 128
