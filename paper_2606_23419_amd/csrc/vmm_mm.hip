@@ -104,8 +104,9 @@ __device__ __forceinline__ void store_digits(uint32_t a, uint32_t dg) {
 // compiler would hold every LDS access it cannot tell apart until they land.
 // It has no register output; whoever reads the LDS bytes waits (vmcnt) first.
 __device__ __forceinline__ void copy_to_lds(uint32_t lds, uint32_t off, v4i rsrc) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
-               ::"s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(off), "s"(rsrc) : "memory", "m0");
+  int m0;                                  // an output: m0 is reserved and can't be a clobber
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen nt lds"
+               : "={m0}"(m0) : "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(off), "s"(rsrc) : "memory");
 }
 
 // The wave's own LDS accesses complete in order: it is enough to keep the

@@ -1,0 +1,17 @@
+"""What the kernel sources ask of the compiler (no GPU needed)."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2606_23419_amd import build as b
+
+
+@pytest.mark.parametrize("src", ["vmm_mm.hip"])
+def test_inline_asm_compiles_without_warnings(src, tmp_path):
+    # an asm block that names a reserved register (m0) as a clobber is undefined
+    flags = [f for f in b.HIPCC_FLAGS if f != "-Werror=inline-asm"]
+    r = subprocess.run([b.hipcc(), *flags, *b.SOURCE_FLAGS.get(src, []), "-c", os.path.join(b.CSRC, src),
+                        "-o", str(tmp_path / "o")], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    assert "warning" not in r.stderr, r.stderr[:2000]
