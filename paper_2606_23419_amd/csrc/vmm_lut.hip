@@ -320,6 +320,9 @@ __global__ __launch_bounds__(kLutThreads) void k_vmm_lut(const uint8_t* __restri
             (__attribute__((address_space(3))) void*)(dst + (i >> (b + 1)) * pad + 8 * i), 16, 0, 0);
     }
   }
+  // the copies have no register that a reader could wait for: every wave waits
+  // for its own before the barrier that lets the others read them
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
 
   for (int i = 16 * wave; i < n_ent; i += kStep * R) {

@@ -1,5 +1,6 @@
 """What the kernel sources ask of the compiler (no GPU needed)."""
 import os
+import re
 import subprocess
 
 import pytest
@@ -15,3 +16,16 @@ def test_inline_asm_compiles_without_warnings(src, tmp_path):
                         "-o", str(tmp_path / "o")], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
     assert "warning" not in r.stderr, r.stderr[:2000]
+
+
+def _code(src):
+    """A kernel source without its comments."""
+    with open(os.path.join(b.CSRC, src)) as f:
+        return re.sub(r"//[^\n]*", "", f.read())
+
+
+def test_lut_copies_are_waited_for_before_the_barrier():
+    # no register depends on a copy to LDS, and a barrier alone does not wait
+    # for copies in flight: the source has to ask for it
+    after = _code("vmm_lut.hip").split("__builtin_amdgcn_global_load_lds(")[-1]
+    assert "s_waitcnt vmcnt(0)" in after.split("__syncthreads()")[0]
