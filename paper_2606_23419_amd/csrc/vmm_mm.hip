@@ -109,6 +109,12 @@ __device__ __forceinline__ void copy_to_lds(uint32_t lds, uint32_t off, v4i rsrc
                : "={m0}"(m0) : "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(off), "s"(rsrc) : "memory");
 }
 
+// v added to *p in one memory instruction, which wait_copies counts (an
+// atomicAdd may become another number of them).
+__device__ __forceinline__ void add_to(float* p, float v) {
+  asm volatile("global_atomic_add_f32 %0, %1, off" ::"v"(p), "v"(v) : "memory");
+}
+
 // The wave's own LDS accesses complete in order: it is enough to keep the
 // compiler from moving them.
 __device__ __forceinline__ void wave_lds_order() {
@@ -359,7 +365,8 @@ __global__ __launch_bounds__(kMmThreads, 4) void k_vmm_mm(
   const float s_e = __builtin_bit_cast(float, (uint32_t)(127 - re * U) << 23);   // 2^(-e U)
 
   for (int col = 0; col < ncol; ++col) {
-    // the first blocks of every list (behind the copies: the last column's adds)
+    // the first blocks of every list (behind the copies: the last column's adds,
+    // one instruction per token; no wave skips one, half its lanes take part at least)
     wait_copies(nlate + (col ? NB : 0));
     lds_barrier();
     const int4 nb4 = *(const int4*)&s_nblk[0];
@@ -443,7 +450,7 @@ __global__ __launch_bounds__(kMmThreads, 4) void k_vmm_mm(
     float* yo = y + (size_t)(c0 + col) * W + wave * OW + o;
 #pragma unroll
     for (int t = 0; t < NB; ++t)
-      if (OW == 64 || (t & 1) == half) atomicAdd(yo + (size_t)t * N, v[t]);   // (two lanes take the tokens in turn)
+      if (OW == 64 || (t & 1) == half) add_to(yo + (size_t)t * N, v[t]);   // (two lanes take the tokens in turn)
   }
 }
 

@@ -29,3 +29,11 @@ def test_lut_copies_are_waited_for_before_the_barrier():
     # for copies in flight: the source has to ask for it
     after = _code("vmm_lut.hip").split("__builtin_amdgcn_global_load_lds(")[-1]
     assert "s_waitcnt vmcnt(0)" in after.split("__syncthreads()")[0]
+
+
+def test_decode_adds_are_one_instruction_each():
+    # the copies are waited for by counting the memory instructions behind them:
+    # the adds of a column are written as the one instruction that is counted
+    code = _code("vmm_mm.hip")
+    assert not re.search(r"\batomicAdd\b|__hip_atomic|unsafeAtomicAdd", code)
+    assert re.search(r'asm volatile\("global_atomic_add_f32 %0, %1, off"', code)
