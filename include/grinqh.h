@@ -231,7 +231,8 @@ GRINQH_API int grinqh_vmm_topk(const grinqh_layer_desc* desc, const void* packed
  *   x: fp16 [M][K] (device, 16-byte aligned), finite; y: fp32 [M][N]
  *   (device, 4-byte aligned); 1 <= M <= 2^24.
  *   flags: 0 -> y is overwritten; GRINQH_VMM_ACCUMULATE -> y += result.
- * The summation order is fixed, so a result is reproducible bit for bit. */
+ * The summation order is fixed, so a result is reproducible bit for bit, and
+ * accumulating adds to y exactly what overwriting would store in it. */
 GRINQH_API int grinqh_prefill(const grinqh_layer_desc* desc, const void* packed_codes,
                               const void* packed_scales, const void* x, int32_t M, float* y,
                               int32_t flags, void* stream);

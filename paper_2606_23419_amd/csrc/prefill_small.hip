@@ -19,8 +19,9 @@
 // waves' partial sums are added in wave order, 16 tokens at a time.
 //
 // Few columns also split K over two workgroups that add into a cleared y: 0 + a
-// + b is the same in either order, so the result still repeats.  (Adding to the
-// caller's y would not: there K stays in one workgroup.)
+// + b is the same in either order, so the result still repeats.  Adding to the
+// caller's y would not: there one workgroup takes both halves of K in turn and
+// adds a + b, so that y grows by exactly what overwriting it would store.
 //
 // Bound by the 16-byte plane pieces a lane reads, a cache line each (about 2.7
 // cycles per piece and CU), and by M from about 40 tokens on by the token loads.
@@ -58,7 +59,9 @@ __device__ __forceinline__ uint32_t weights2(uint32_t q, uint32_t a, uint32_t b,
 // pos / 2 holds outputs 8 (j & 1) + (j >> 1) and that + 4.
 __device__ __forceinline__ int output_at(int pos) { return 8 * ((pos >> 1) & 1) + (pos >> 2) + 4 * (pos & 1); }
 
-template <int U, int MT, int CW>
+// HALVES: halves of K that a workgroup takes, one after the other (2 only
+// without CW, and then gridDim.y is 1).
+template <int U, int MT, int CW, int HALVES>
 __global__ __launch_bounds__(64 * kPsWaves, 2) void k_prefill_small(
     const uint8_t* __restrict__ codes, const uint16_t* __restrict__ scales, const uint16_t* __restrict__ x,
     float* __restrict__ y, Layer L, int M, int accumulate, int row_blocks) {
@@ -68,6 +71,8 @@ __global__ __launch_bounds__(64 * kPsWaves, 2) void k_prefill_small(
   constexpr int P = 8 / U;                 // planes of the widest code
   constexpr int WD = U * C / 2;            // dwords of the outputs in a plane row
   constexpr int RED = kPsN + 4;            // floats of a token's row of partial sums
+  constexpr int OUTS = CW * 16 * kPsN / (64 * kPsWaves);   // outputs of 16 tokens per thread
+  static_assert(HALVES == 1 || CW == 1, "two columns are never split");
   __shared__ __align__(16) uint8_t s_w[kPsWaves][kPsK * kPsRow];
   static_assert(sizeof(s_w) >= kPsWaves * 16 * RED * 4, "the partial sums reuse the tiles");
 
@@ -88,8 +93,8 @@ __global__ __launch_bounds__(64 * kPsWaves, 2) void k_prefill_small(
   const int n0 = (ctile * CW + cw) * kPsN, m0 = rblk * 16 * MT;
   const int K = L.K, tile = n0 / L.T, o0 = n0 - tile * L.T;
   const int np = L.P, plane_bytes = L.T * U / 8;
-  // this workgroup's turns of 64 channels: all, or every other 8 (K split in two)
-  const int turns = K / kPsK, first = kw + KW * (int)blockIdx.y, stride = KW * (int)gridDim.y;
+  // this workgroup's turns of 64 channels: all, or every other 8 (a half of K)
+  const int turns = K / kPsK, stride = KW * (int)gridDim.y * HALVES;
   const int i16 = lane & 15, h = lane >> 4;
 
   const uint8_t* wsrc = codes + ((size_t)tile * K + lane) * L.RB + o0 * U / 8;
@@ -115,11 +120,6 @@ __global__ __launch_bounds__(64 * kPsWaves, 2) void k_prefill_small(
   };
 
   float4v acc[MT][C];
-#pragma unroll
-  for (int m = 0; m < MT; ++m)
-#pragma unroll
-    for (int n = 0; n < C; ++n) acc[m][n] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
-
   uint8_t* tile_w = s_w[wave];
   const __attribute__((address_space(3))) uint8_t* rd =
       (const __attribute__((address_space(3))) uint8_t*)tile_w + (8 * h + (i16 >> 2)) * kPsRow + 8 * (i16 & 3);
@@ -175,48 +175,65 @@ __global__ __launch_bounds__(64 * kPsWaves, 2) void k_prefill_small(
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   };
 
-  if (first < turns) {
-    // past the last turn the last one is loaded again (in bounds, never used)
-    const int last = first + (turns - 1 - first) / stride * stride;
-    Turn ra, rb;
-    load(ra, first);
-    int t = first;
-    // (no condition around a consume: the compiler would move its loads there)
-    for (; t + stride < turns; t += 2 * stride) {
-      load(rb, t + stride);
-      __builtin_amdgcn_sched_barrier(0);   // the loads go out first
-      consume(ra);
-      load(ra, min(t + 2 * stride, last));
-      __builtin_amdgcn_sched_barrier(0);
-      consume(rb);
+  float kept[HALVES > 1 ? MT : 1][OUTS];   // the first half's sums
+#pragma unroll 1
+  for (int half = 0; half < HALVES; ++half) {
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int n = 0; n < C; ++n) acc[m][n] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
+    const int first = kw + KW * (int)(HALVES > 1 ? half : blockIdx.y);
+    if (half) __syncthreads();             // the partial sums are read: the tiles are free
+    if (first < turns) {
+      // past the last turn the last one is loaded again (in bounds, never used)
+      const int last = first + (turns - 1 - first) / stride * stride;
+      Turn ra, rb;
+      load(ra, first);
+      int t = first;
+      // (no condition around a consume: the compiler would move its loads there)
+      for (; t + stride < turns; t += 2 * stride) {
+        load(rb, t + stride);
+        __builtin_amdgcn_sched_barrier(0);   // the loads go out first
+        consume(ra);
+        load(ra, min(t + 2 * stride, last));
+        __builtin_amdgcn_sched_barrier(0);
+        consume(rb);
+      }
+      if (t < turns) consume(ra);
     }
-    if (t < turns) consume(ra);
-  }
 
-  // ---- the waves' sums, 16 tokens at a time: element r of lane l is token 4 h
-  // + r, place i16 of the chunk
-  float* red = (float*)&s_w[0][0];
+    // ---- the waves' sums, 16 tokens at a time: element r of lane l is token 4 h
+    // + r, place i16 of the chunk
+    float* red = (float*)&s_w[0][0];
 #pragma unroll
-  for (int m = 0; m < MT; ++m) {
-    __syncthreads();
+    for (int m = 0; m < MT; ++m) {
+      __syncthreads();
 #pragma unroll
-    for (int n = 0; n < C; ++n)
+      for (int n = 0; n < C; ++n)
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        red[(wave * 16 + 4 * h + r) * RED + 16 * n + output_at(i16)] = acc[m][n][r];
-    __syncthreads();
+        for (int r = 0; r < 4; ++r)
+          red[(wave * 16 + 4 * h + r) * RED + 16 * n + output_at(i16)] = acc[m][n][r];
+      __syncthreads();
 #pragma unroll
-    for (int i = 0; i < CW * 16 * kPsN / (64 * kPsWaves); ++i) {
-      const int e = tid + i * 64 * kPsWaves, row = e / (CW * kPsN), cc = e / kPsN % CW, col = e % kPsN;
-      float v = 0.0f;
+      for (int i = 0; i < OUTS; ++i) {
+        const int e = tid + i * 64 * kPsWaves, row = e / (CW * kPsN), cc = e / kPsN % CW, col = e % kPsN;
+        float v = 0.0f;
 #pragma unroll
-      for (int w = 0; w < KW; ++w) v += red[((w * CW + cc) * 16 + row) * RED + col];
-      v *= L.sfac;                         // 8-bit code units -> b_max units (exact)
-      const int mm = m0 + 16 * m + row;
-      if (mm < M) {
-        float* dst = y + (size_t)mm * L.N + (ctile * CW + cc) * kPsN + col;
-        if (gridDim.y == 2) atomicAdd(dst, v);   // the other half adds too: 0 + a + b in either order
-        else *dst = accumulate ? *dst + v : v;
+        for (int w = 0; w < KW; ++w) v += red[((w * CW + cc) * 16 + row) * RED + col];
+        v *= L.sfac;                       // 8-bit code units -> b_max units (exact)
+        if constexpr (HALVES > 1) {
+          if (half == 0) {
+            kept[m][i] = v;
+            continue;
+          }
+          v += 0.0f + kept[m][i];          // as in a cleared y
+        }
+        const int mm = m0 + 16 * m + row;
+        if (mm < M) {
+          float* dst = y + (size_t)mm * L.N + (ctile * CW + cc) * kPsN + col;
+          if (gridDim.y == 2) atomicAdd(dst, v);   // the other half adds too: 0 + a + b in either order
+          else *dst = accumulate ? *dst + v : v;
+        }
       }
     }
   }
@@ -227,12 +244,12 @@ __global__ __launch_bounds__(256) void k_zero_prefill(float* __restrict__ y, lon
   if (i < n) y[i] = 0.0f;
 }
 
-template <int U, int CW>
+template <int U, int CW, int HALVES>
 void launch_mt(int mt, dim3 grid, hipStream_t s, const void* codes, const void* scales, const void* x, int M,
                float* y, int accumulate, const Layer& L, int row_blocks) {
 #define GRINQH_PS(MM)                                                                                       \
   case MM:                                                                                                  \
-    hipLaunchKernelGGL((k_prefill_small<U, MM, CW>), grid, dim3(64 * kPsWaves), 0, s, (const uint8_t*)codes,  \
+    hipLaunchKernelGGL((k_prefill_small<U, MM, CW, HALVES>), grid, dim3(64 * kPsWaves), 0, s, (const uint8_t*)codes,  \
                        (const uint16_t*)scales, (const uint16_t*)x, y, L, M, accumulate, row_blocks);       \
     break;
   switch (mt) { GRINQH_PS(1) GRINQH_PS(2) GRINQH_PS(3) GRINQH_PS(4) GRINQH_PS(5) }
@@ -275,7 +292,8 @@ int launch_prefill_small(const Layer& L, const void* codes, const void* scales, 
   // 4096 -> 4096, M = 77 and 27 against 36 at M = 128; above, 4096 -> 6144 at M = 128 has 192
   // workgroups and took 51 split, 40 not)
   const int cw = wgs > 256 ? 2 : 1;
-  const int split = !accumulate && wgs <= 128 ? 2 : 1;
+  const bool halves = wgs <= 128;
+  const int split = halves && !accumulate ? 2 : 1;   // else one workgroup takes both halves in turn
   const dim3 grid((unsigned)(L.N / (kPsN * cw) * row_blocks), (unsigned)split);
   if (split == 2) {
     const long n = (long)M * L.N;
@@ -283,13 +301,15 @@ int launch_prefill_small(const Layer& L, const void* codes, const void* scales, 
     const int st = check_launch("prefill zero-fill");
     if (st) return st;
   }
-#define GRINQH_PS(UU, CC) launch_mt<UU, CC>(mt, grid, s, codes, scales, x, M, y, accumulate, L, row_blocks)
+#define GRINQH_PS(UU, CC, HH) launch_mt<UU, CC, HH>(mt, grid, s, codes, scales, x, M, y, accumulate, L, row_blocks)
   if (L.u == 2) {
-    if (cw == 2) GRINQH_PS(2, 2);
-    else GRINQH_PS(2, 1);
+    if (cw == 2) GRINQH_PS(2, 2, 1);
+    else if (halves && accumulate) GRINQH_PS(2, 1, 2);
+    else GRINQH_PS(2, 1, 1);
   } else {
-    if (cw == 2) GRINQH_PS(1, 2);
-    else GRINQH_PS(1, 1);
+    if (cw == 2) GRINQH_PS(1, 2, 1);
+    else if (halves && accumulate) GRINQH_PS(1, 1, 2);
+    else GRINQH_PS(1, 1, 1);
   }
 #undef GRINQH_PS
   return check_launch("prefill (short)");

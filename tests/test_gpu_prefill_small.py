@@ -57,3 +57,19 @@ def test_prefill_small_rows_past_m_are_not_written(g, torch):  # noqa: F811
     buf = torch.full((M + 13, 512), 7.0, device="cuda")
     g.grinqh_prefill(L.desc, L.pc, L.ps, _dev(torch, inputs.activations_t3(256, M, 97)), y=buf[:M])
     assert bool((buf[M:] == 7.0).all())
+
+
+@pytest.mark.parametrize("K,N,levels,M", [
+    (1024, 512, (0, 2, 4, 8), 150), (1152, 1024, (0, 2, 4, 6, 8), 1), (14336, 512, (0, 2, 4, 6, 8), 77),
+    (1024, 1024, (0, 2, 3, 4, 8), 20), (640, 512, (0, 2, 4), 47), (896, 2048, (0, 2, 4, 8), 64),
+    (2048, 8192, (0, 2, 4, 8), 100), (256, 16640, (0, 2, 4, 8), 18)])
+def test_prefill_small_adds_what_it_would_store(g, torch, K, N, levels, M):  # noqa: F811
+    # accumulating grows y by the overwriting result, bit for bit, whether the
+    # halves of K go to two workgroups, to one in turn, or K is not halved
+    L = Layer(g, torch, K, N, levels, cfg=98, codes_src=True)
+    xd = _dev(torch, inputs.activations_t3(K, M, 98))
+    y1 = g.grinqh_prefill(L.desc, L.pc, L.ps, xd)
+    base = torch.randn((M, N), generator=torch.Generator("cuda").manual_seed(98), device="cuda")
+    y2 = base.clone()
+    g.grinqh_prefill(L.desc, L.pc, L.ps, xd, y=y2, accumulate=True)
+    assert torch.equal(y2, base + y1)
