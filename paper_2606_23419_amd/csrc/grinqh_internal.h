@@ -127,6 +127,8 @@ int launch_vmm(const Layer& L, const void* codes, const void* scales, const void
                int B, float* y, int accumulate, hipStream_t s);
 int launch_prefill(const Layer& L, const void* codes, const void* scales, const void* x, int M,
                    float* y, int accumulate, hipStream_t s);
+// prefill.hip's choice of 256 x 256 tiles: about 0.6 of them per CU or more
+inline bool prefill_wide(const Layer& L, long M) { return (M + 255) / 256 * (L.N / 256) >= 160; }
 bool prefill_small_takes(const Layer& L, int M);
 int launch_prefill_small(const Layer& L, const void* codes, const void* scales, const void* x, int M,
                          float* y, int accumulate, hipStream_t s);

@@ -391,7 +391,7 @@ int launch_prefill(const Layer& L, const void* codes, const void* scales, const 
   if (!option(&Options::prefill_tile) && prefill_small_takes(L, M))
     return launch_prefill_small(L, codes, scales, x, M, y, accumulate, s);
   const long mb256 = (M + 255) / 256;
-  int cfg = mb256 * (L.N / 256) >= 160 ? 0 : mb256 * (L.N / 128) >= 160 ? 1 : 2;
+  int cfg = prefill_wide(L, M) ? 0 : mb256 * (L.N / 128) >= 160 ? 1 : 2;
   int n_split = 0;   // columns of the 256 x 256 part when split
   if (const int v = option(&Options::prefill_tile)) {
     cfg = v - 1;

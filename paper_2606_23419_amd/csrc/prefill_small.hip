@@ -272,14 +272,34 @@ struct Blocks {
 
 }  // namespace
 
-// One block of tokens always (4096 -> 28672 at M = 77: 82 us against 98), more as long as
-// one workgroup per 64 outputs and block leaves a single round on the chip:
-// 4096 -> 4096 at M = 256 (256 workgroups) 39 us against 63, 14336 -> 4096 111 against 211,
-// 4096 -> 6144 at M = 128 (192) 40 against 65 but at M = 256 (384) 72 against 65.
+// One block of tokens (M <= 80) while the workgroups of 128 outputs are a single
+// round of one per CU, or prefill.hip would take its narrower tiles: 32768
+// outputs on 256 CUs, M = 80, 4096 channels 68 us against 86, 33792 outputs 135
+// against 160.  Past that prefill.hip covers 256 outputs per CU and round, and
+// this kernel is still ahead
+//   - up to 48 tokens: 65536 outputs, M = 48: 1024 / 4096 channels 37 / 131 us
+//     against 41 / 147; 131072 outputs 71 / 264 against 82 / 295;
+//   - where its rounds are fewer than twice prefill.hip's, to 64 tokens or with
+//     rows under 8 bits: 81920 outputs, M = 64: 60 / 207 against 67 / 226, at 4 bits and
+//     M = 80 64 / 176 against 66 / 217; but at 8 bits and M = 80 68 / 236 against 68 / 227;
+//   - to 64 tokens where K is long: 65536 outputs, M = 64: 4096 channels 141 against
+//     147, 131072 outputs 287 against 303; but 1024 channels 43 against 42;
+// and not otherwise: M = 77..80: 65536 outputs, 1024 / 4096 channels 48 / 156 against
+// 42 / 146, 131072 outputs 92 / 316 against 85 / 298, 1-bit planes 59 / 186 against 53 / 177.
+// More blocks as long as one workgroup per 64 outputs and block leaves a single
+// round on the chip: 4096 -> 4096 at M = 256 (256 workgroups) 39 us against 63,
+// 14336 -> 4096 111 against 211, 4096 -> 6144 at M = 128 (192) 40 against 65 but at
+// M = 256 (384) 72 against 65.
 bool prefill_small_takes(const Layer& L, int M) {
   if (M > 80 * 256) return false;
   const Blocks b(M);
-  return b.rows == 1 || (long)(L.N / kPsN) * b.rows <= 256;
+  const long cus = device_cus();
+  if (b.rows > 1) return (long)(L.N / kPsN) * b.rows <= cus;
+  const long rounds = (L.N / (2 * kPsN) + cus - 1) / cus;
+  if (rounds == 1 || !prefill_wide(L, M)) return true;
+  const long wide = (L.N / 256 + cus - 1) / cus;   // prefill.hip's
+  if (b.mt <= 3 || (b.mt == 4 && L.K >= 4096)) return true;
+  return rounds < 2 * wide && (b.mt == 4 || L.bmax < 8);
 }
 
 int launch_prefill_small(const Layer& L, const void* codes, const void* scales, const void* x, int M, float* y,
@@ -290,9 +310,10 @@ int launch_prefill_small(const Layer& L, const void* codes, const void* scales, 
   // more than a round of workgroups: two columns share one (82 against 94 us at
   // 4096 -> 28672, M = 77); at most half a round: K split in two (28 against 42 us at
   // 4096 -> 4096, M = 77 and 27 against 36 at M = 128; above, 4096 -> 6144 at M = 128 has 192
-  // workgroups and took 51 split, 40 not)
-  const int cw = wgs > 256 ? 2 : 1;
-  const bool halves = wgs <= 128;
+  // workgroups of 256 CUs and took 51 split, 40 not)
+  const int cus = device_cus();
+  const int cw = wgs > cus ? 2 : 1;
+  const bool halves = wgs <= cus / 2;
   const int split = halves && !accumulate ? 2 : 1;   // else one workgroup takes both halves in turn
   const dim3 grid((unsigned)(L.N / (kPsN * cw) * row_blocks), (unsigned)split);
   if (split == 2) {

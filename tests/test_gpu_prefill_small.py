@@ -4,7 +4,7 @@ import pytest
 
 from oracle import grinqh_oracle as orc
 from synth import inputs
-from test_gpu_parity import Layer, _dev, _host, g, torch  # noqa: F401
+from test_gpu_parity import Layer, _dev, _host, g, opts, torch  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -73,3 +73,20 @@ def test_prefill_small_adds_what_it_would_store(g, torch, K, N, levels, M):  # n
     y2 = base.clone()
     g.grinqh_prefill(L.desc, L.pc, L.ps, xd, y=y2, accumulate=True)
     assert torch.equal(y2, base + y1)
+
+
+@pytest.mark.parametrize("levels,K,M,small", [
+    ((0, 2, 4, 8), 256, 65, False), ((0, 2, 4, 8), 256, 49, False), ((0, 2, 3, 4, 8), 256, 80, False),
+    ((0, 2, 4, 8), 256, 48, True)])
+def test_prefill_small_leaves_a_second_round_to_the_wide_tiles(g, torch, opts, levels, K, M, small):  # noqa: F811
+    # 256 outputs per CU: two rounds of 128-output workgroups, one of 256 x 256
+    # tiles, whose sums come in another order
+    N = 256 * torch.cuda.get_device_properties(0).multi_processor_count
+    L = Layer(g, torch, K, N, levels, cfg=99, codes_src=True)
+    xd = _dev(torch, inputs.activations_t3(K, M, 99))
+    y = g.grinqh_prefill(L.desc, L.pc, L.ps, xd)
+    opts(g.GRINQH_OPT_PREFILL_TILE, 1)
+    wide = g.grinqh_prefill(L.desc, L.pc, L.ps, xd)
+    assert torch.equal(y, wide) == (not small)
+    ref = orc.prefill(L.codes[:512], L.scales[:, :512], inputs.activations_t3(K, M, 99))
+    assert np.abs(_host(y)[:, :512] - ref).max() <= 1e-3 * np.abs(ref).max()
