@@ -186,7 +186,12 @@ GRINQH_API int grinqh_assign(const grinqh_layer_desc* desc, int mode, const void
  *   -> y += result (the caller initialised y, e.g. once for many VMMs into
  *   one buffer).  Accumulation order across K is not fixed, so y is
  *   reproducible to rounding, not bit for bit.  Any other flag bit is
- *   GRINQH_EINVAL. */
+ *   GRINQH_EINVAL.
+ *   Precision: products and sums are at least those of fp32.  The matrix-core
+ *   kernel holds each group's x in fixed point, 24 bits (23 for 1-bit planes)
+ *   at the group's largest active |x|: a channel is exact down to 2^-13
+ *   (2^-12) of that, and what the group's smaller channels lose together is at
+ *   most 2^-22 (2^-21) of it. */
 GRINQH_API int grinqh_vmm(const grinqh_layer_desc* desc, const void* packed_codes,
                const void* packed_scales, const void* x, const uint8_t* level_map,
                int32_t B, float* y, int32_t flags, void* workspace, size_t ws_bytes,

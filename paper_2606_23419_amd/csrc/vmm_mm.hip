@@ -22,7 +22,10 @@
 //     by 2^(-e*U) at the end.
 //   - x becomes a fixed-point integer X = rne(x 2^s), s from the largest |x|
 //     of the group so that |X| < 2^24 (2^23 for 1-bit planes): an fp32-like 24
-//     bits at the largest channel, exact down to 2^-13 of it.  For a row of
+//     bits at the largest channel, exact down to 2^-13 of it (2^-12).  beta is
+//     made of the same X.  Where the channels below that lose more than 2 units
+//     of X together, add_rests puts back what they lost: so a group's x is
+//     exact but for at most 2^-22 (2^-21) of its largest |x|, in all.  For a row of
 //     plane j, X is shifted to the plane's weight 2^(8 - j U) and cut into four
 //     balanced int8 digits; the digits of the NB tokens are the columns (4 NB
 //     <= 16) of the B operand.  A token's digits are zero on planes beyond its
@@ -44,6 +47,10 @@
 // workgroups per CU instead of three); four waves, one group per workgroup
 // without lists (18.6); float accumulation on v_mfma_scale_f32_16x16x128 with
 // fp4 fields and x cut into bf8 terms (sums rounded to about 18 bits).
+//
+// add_rests costs such a workgroup some microseconds.  No group needs it where
+// the smallest activations are skipped (Student-t and SwiGLU x, 20% at level 0);
+// with every channel active 0.01% of the groups do (0.06% with 1-bit planes).
 //
 // Per group and output y_n += s_{g,n} (sum_k X_k t_k 2^-s + beta_g), t_k the
 // code truncated to the channel's level (8-bit units), beta_g = sum over
@@ -178,6 +185,49 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+constexpr float kRestMax = 2.0f;         // units of X
+
+// What rounding to X left of x, for one token and the W outputs from n0 on:
+//   y_n += s_n sum_k rest_k (t_k + phi_b - 128) unit,  rest_k = x_k to_fix - X_k
+// in units of X.  depth: planes read per channel (0: none), valid in lists with
+// left > 0.  All threads call it, after a barrier; sum: W floats of LDS.
+template <int U, int W, int PL>
+__device__ __forceinline__ void add_rests(const uint16_t* x, const uint8_t* rows, const uint16_t* scales, float* y,
+                                          const uint8_t* depth, const float* left, int left_stride, float* sum, float to_fix,
+                                          float unit, int RB, int plane_bytes, int bmax) {
+  constexpr int CW = W / 16;               // 16 outputs per thread, 16 or 32 rows at once
+  const int tid = threadIdx.x, o0 = 16 * (tid % CW);
+  for (int o = tid; o < W; o += kMmThreads) sum[o] = 0.0f;
+  lds_barrier();
+  float acc[16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
+#pragma unroll 1
+  for (int r = tid / CW; r < kGroup; r += kMmThreads / CW) {
+    const float fix = h2f(x[r]) * to_fix, rest = fix - rintf(fix);
+    const int d = left[(r >> 5) * left_stride] > 0.0f && rest != 0.0f ? depth[r] : 0;
+    const uint8_t* row = rows + (size_t)r * RB + o0 * U / 8;
+    uint32_t m[PL], c[4], q[4];            // planes; 2-bit fields; codes: byte i of q[j] is output 4 i + j
+#pragma unroll
+    for (int p = 0; p < PL; ++p)
+      m[p] = p >= d ? 0u : U == 2 ? *(const uint32_t*)(row + p * plane_bytes) : *(const uint16_t*)(row + p * plane_bytes);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if constexpr (U == 2) c[j] = j < PL ? m[j] : 0u;
+      else c[j] = 2 * j < PL ? spread_bits(m[2 * j]) << 1 | spread_bits(m[2 * j + 1]) : 0u;
+    }
+    assemble_codes(c[0], c[1], c[2], c[3], q);
+    const float v = d ? rest : 0.0f, off = v * phi_minus_offset(U * d, bmax);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] += fmaf(v, (float)((q[e & 3] >> (8 * (e >> 2))) & 0xFFu), off);
+  }
+#pragma unroll
+  for (int e = 0; e < 16; ++e) atomicAdd(&sum[o0 + e], acc[e]);
+  lds_barrier();
+  for (int o = tid; o < W; o += kMmThreads) atomicAdd(&y[o], h2f(scales[o]) * unit * sum[o]);
+  lds_barrier();
+}
+
 template <int U, int W, int PL, int NB, bool TOPK>
 __global__ __launch_bounds__(kMmThreads, 4) void k_vmm_mm(
     const uint16_t* __restrict__ x, const uint8_t* __restrict__ lm, int K, int fused, int run,
@@ -193,6 +243,8 @@ __global__ __launch_bounds__(kMmThreads, 4) void k_vmm_mm(
   __shared__ __align__(16) uint16_t s_list[4][16][MAXB];   // row offsets / 64: row r of block b at [r][b]
   __shared__ __align__(16) float s_beta[NB][4];
   __shared__ __align__(16) int s_nblk[4];
+  __shared__ __align__(16) float s_left[4][NB == 3 ? 4 : NB];   // per list: sum of |x to_fix - X|
+  __shared__ __align__(16) uint8_t s_depth[NB][kGroup];    // where that is not zero
   static_assert(!TOPK || sizeof(topksel::Scratch) <= sizeof(s_w), "the selection's scratch lies over the weights' place");
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -315,6 +367,7 @@ __global__ __launch_bounds__(kMmThreads, 4) void k_vmm_mm(
   // ---- the B operand, while the copies are in flight
   constexpr int FIX = U == 2 ? 38 : 37;    // X = rne(x 2^(FIX - e)), |x| < 2^(e - 14)
   uint32_t e_max[NB];
+  float rest[NB], most = 0.0f;             // what X leaves of the channel's x, in units of X
 #pragma unroll
   for (int t = 0; t < NB; ++t) {
     const uint32_t a = xm[t] & 0x7FFF7FFFu;
@@ -327,12 +380,16 @@ __global__ __launch_bounds__(kMmThreads, 4) void k_vmm_mm(
     e_max[t] = mx >> 10 ? mx >> 10 : 1u;
     const float to_fix = __builtin_bit_cast(float, (127u + FIX - e_max[t]) << 23);
     const float fx = h2f((uint16_t)xc[t]);
-    const int X = cvt_i32(rintf(fx * to_fix));
+    const float Xf = rintf(fx * to_fix);
+    const int X = cvt_i32(Xf);
     if (sub == 0) {
       // fx * 0 carries an infinite or NaN x of an active channel into every output
       const float phi = phi_minus_offset(U * d[t], bmax);
-      const float beta = half_sum_dpp(d[t] ? fmaf(fx, phi, fx * 0.0f) : 0.0f);
+      const float unfix = __builtin_bit_cast(float, (127u - FIX + e_max[t]) << 23);
+      const float beta = half_sum_dpp(d[t] ? fmaf(Xf * unfix, phi, fx * 0.0f) : 0.0f);
       if (lane == 0) s_beta[t][list] = beta;
+      rest[t] = d[t] ? fabsf(fx * to_fix - Xf) : 0.0f;
+      most = fmaxf(most, rest[t]);
     }
     // the list's half waves take its planes in turn
 #pragma unroll
@@ -348,6 +405,20 @@ __global__ __launch_bounds__(kMmThreads, 4) void k_vmm_mm(
         store_digits<COLB>(lds_addr(s_b) + (uint32_t)(4 * t * COLB + 16 * list + pos), dg);
       }
     }
+  }
+
+  if (sub == 0) {
+    float left[NB];
+#pragma unroll
+    for (int t = 0; t < NB; ++t) left[t] = 0.0f;
+    if (__builtin_expect(__ballot(most > 0.0f) != 0, 0)) {
+#pragma unroll
+      for (int t = 0; t < NB; ++t) {
+        left[t] = half_sum_dpp(rest[t]);
+        if (half == 0) s_depth[t][ch] = (uint8_t)d[t];
+      }
+    }
+    if (lane == 0) __builtin_memcpy(s_left[list], left, sizeof(left));
   }
 
   // ---- the columns
@@ -451,6 +522,29 @@ __global__ __launch_bounds__(kMmThreads, 4) void k_vmm_mm(
 #pragma unroll
     for (int t = 0; t < NB; ++t)
       if (OW == 64 || (t & 1) == half) add_to(yo + (size_t)t * N, v[t]);   // (two lanes take the tokens in turn)
+  }
+
+  // ---- groups whose x is not exact enough
+  float lost[NB];                          // (a token with an active infinity or NaN: NaN, left out)
+#pragma unroll
+  for (int t = 0; t < NB; ++t) lost[t] = (s_left[0][t] + s_left[1][t]) + (s_left[2][t] + s_left[3][t]);
+  float worst = lost[0];
+#pragma unroll
+  for (int t = 1; t < NB; ++t) worst = fmaxf(worst, lost[t]);
+  if (__builtin_expect(worst > kRestMax, 0)) {
+    lds_barrier();                         // the digit sums are read: their place is free
+#pragma unroll 1
+    for (int i = 0; i < ncol * NB; ++i) {
+      const int t = i % NB, n0 = (c0 + i / NB) * W, tile = n0 >> A.log2_T, ob = (n0 & (T - 1)) * U / 8;
+      uint32_t e = e_max[0];
+#pragma unroll
+      for (int j = 1; j < NB; ++j) e = t == j ? e_max[j] : e;
+      add_rests<U, W, PL>(x + (size_t)t * K + k0, codes + ((size_t)tile * K + k0) * RB + ob,
+                          scales + (size_t)blockIdx.y * N + n0, y + (size_t)t * N + n0, s_depth[t], &s_left[0][t],
+                          (int)(sizeof(s_left[0]) / 4),
+                          (float*)s_w, __builtin_bit_cast(float, (127u + FIX - e) << 23),
+                          __builtin_bit_cast(float, (127u - FIX + e) << 23) * A.sfac, RB, T * U / 8, bmax);
+    }
   }
 }
 

@@ -25,14 +25,17 @@ def _maps(kind, B, K, top, seed):
 
 
 def _bound(L, x, lm, u):
-    """Per output: X is rounded to 2^-25 of a power of two at most twice the
-    group's largest active |x| (2^-24 for 1-bit planes), each channel's code
-    is at most 255 (8-bit units), and a group's sum takes fewer than 16 float32
-    roundings, plus one per group in the adds."""
+    """Per output: a unit of X is 2^-24 of a power of two at most twice the
+    group's largest active |x| (2^-23 for 1-bit planes); what a group's X leave
+    of x is at most half a unit per channel and two in all, times a weight of
+    at most 128 (8-bit units); and a group's sum takes fewer than 16 float32
+    roundings of sums of x times codes of at most 255, plus one per group in
+    the adds."""
     G = L.K // 128
     xa = np.abs(x.astype(np.float64)) * (lm > 0)
     xa = xa.reshape(-1, G, 128)
-    per = (lm.reshape(-1, G, 128) > 0).sum(2) * xa.max(2) * (2 if u == 1 else 1) + (16 + G) * xa.sum(2)
+    left = np.minimum((lm.reshape(-1, G, 128) > 0).sum(2), 4) / 2
+    per = left * xa.max(2) * (2 if u == 1 else 1) + (16 + G) * xa.sum(2)
     s = L.scales.astype(np.float64) * 2.0 ** (L.b_max - 8)
     return 2.0 ** -24 * 255 * per @ s
 
@@ -93,3 +96,47 @@ def test_vmm_mm_skipped_and_non_finite(g, torch, levels, B):  # noqa: F811
         y = _host(g.grinqh_vmm(L.desc, L.pc, L.ps, _dev(torch, bad), _dev(torch, lm)))
         assert not np.isfinite(y[0]).any()
         assert np.all(np.abs(y[1:] - ref[1:]) <= bound[1:])
+
+
+WIDE = [(256, 256, (0, 2, 4, 8), 256, 1), (256, 1024, (0, 2, 4, 6, 8), 1024, 1), (256, 512, (0, 2, 4, 6, 8), 512, 4),
+        (384, 512, (0, 2, 4), 512, 2), (256, 2048, (0, 2, 4, 6), 2048, 3),
+        (256, 1024, (0, 2, 3, 4, 8), 512, 1), (256, 1024, (0, 2, 3, 4, 8), 1024, 4), (256, 512, (0, 1, 2, 3, 4), 512, 2)]
+
+
+@pytest.mark.parametrize("small", ["half", "ramp", "wide"])
+@pytest.mark.parametrize("K,N,levels,tile_n,B,mode", [w + (m,) for w in WIDE for m in ("map", "threshold")] +
+                         [w + ("topk",) for w in WIDE[:2]])
+def test_vmm_mm_wide_range_in_a_group(g, torch, K, N, levels, tile_n, B, small, mode):  # noqa: F811
+    # one channel of a group far above the others, its weight near zero: the
+    # others' x has to reach the sums although it is below the units of the
+    # largest one's 24 bits (all of one sign and to one side, so that losses add up)
+    L = Layer(g, torch, K, N, levels, cfg=100, tile_n=tile_n, codes_src=True)
+    top, half = len(levels) - 1, 1 << (L.b_max - 1)
+    L.codes[:, 5] = half
+    L.pc, L.ps = g.grinqh_pack(L.desc, codes=_dev(torch, L.codes),
+                               scales=_dev(torch, np.ascontiguousarray(L.scales.T)))
+    r = np.random.default_rng(100)
+    x = np.zeros((B, K), np.float16)
+    unit = 2.0 ** (-8 if L.desc.plane_bits == 2 else -7)      # of X beside 32768
+    for t in range(B):
+        x[t] = {"half": np.full(K, unit / 2), "ramp": unit * np.linspace(0.1, 9.6, K),
+                "wide": unit * np.exp2(r.uniform(-14, 8, K))}[small].astype(np.float16)
+        x[t, 5] = 32768.0 if t < 3 else 2.0 ** -3             # (the last token: an ordinary range)
+    xd = _dev(torch, x)
+    if mode == "map":
+        lm = np.full((B, K), top, np.uint8)
+        lm[:, K - 1] = 0
+        lm[:, 40:60] = r.integers(0, top + 1, size=(B, 20))
+        y = g.grinqh_vmm(L.desc, L.pc, L.ps, xd, _dev(torch, lm))
+    elif mode == "threshold":
+        th = np.quantile(np.abs(x[0].astype(np.float64)), np.linspace(0.05, 0.4, top)).astype(np.float32)
+        lm = orc.assign_threshold(x, th)
+        y = g.grinqh_vmm_threshold(L.desc, L.pc, L.ps, xd, th)
+    else:
+        counts = g.grinqh_topk_counts(K, [500] + [9500 // top] * (top - 1) + [9500 - 9500 // top * (top - 1)])
+        lm = orc.assign_topk(x, counts)
+        y = g.grinqh_vmm_topk(L.desc, L.pc, L.ps, xd, counts)
+    ref = orc.vmm_batch(L.codes, L.scales, x, lm, levels)
+    err = np.abs(_host(y) - ref)
+    bound = _bound(L, x, lm, L.desc.plane_bits)
+    assert np.all(err <= bound), (np.max(err / bound), np.abs(ref).max())

@@ -35,5 +35,6 @@ def test_decode_adds_are_one_instruction_each():
     # the copies are waited for by counting the memory instructions behind them:
     # the adds of a column are written as the one instruction that is counted
     code = _code("vmm_mm.hip")
-    assert not re.search(r"\batomicAdd\b|__hip_atomic|unsafeAtomicAdd", code)
+    columns = code.split("wait_copies(nlate")[1].split("float lost")[0]
+    assert "add_to(yo" in columns and not re.search(r"\batomicAdd\b|__hip_atomic|unsafeAtomicAdd", columns)
     assert re.search(r'asm volatile\("global_atomic_add_f32 %0, %1, off"', code)
