@@ -42,8 +42,10 @@ typedef int v2i __attribute__((ext_vector_type(2)));
 // significands, so any other quotient is at least 2^-13 from the nearest
 // rounding boundary: neither this error nor that of adding h (2^-17) moves it
 // across, and boundaries themselves round to even in both.  s = 0: inv = 0 and
-// every code is h.
-__device__ __forceinline__ void quantise8(const uint32_t (&w)[4], float s, float inv, float h,
+// every code is h.  Not finite, as the quotient gives it: a NaN (w, or inf / inf)
+// is code 0 (lo; h where s = 0); beside an infinity (the caller passes s = inv =
+// 0) the rest are h.
+__device__ __forceinline__ void quantise8(const uint32_t (&w)[4], float s, float inv, float h, float lo,
                                           uint32_t (&q)[2]) {
   q[0] = q[1] = 0u;
 #pragma unroll
@@ -52,7 +54,7 @@ __device__ __forceinline__ void quantise8(const uint32_t (&w)[4], float s, float
     const float r = x * inv;
     const float e = fmaf(-r, s, x);
     float c = rintf(fmaf(e, inv, r) + h);
-    c = __builtin_amdgcn_fmed3f(c, 0.0f, 2.0f * h - 1.0f);
+    c = __builtin_amdgcn_fmed3f(c, lo, 2.0f * h - 1.0f);   // a NaN: lo
     q[i / 4] |= (uint32_t)c << (8 * (i % 4));
   }
 }
@@ -105,15 +107,21 @@ __global__ __launch_bounds__(OUT) void k_pack(const void* __restrict__ src, uint
     if constexpr (FP16) {
       uint32_t w[4];
       load_elems<ALIGNED, uint16_t, 8>((const uint16_t*)src + at, w);
-      u16x2 m = __builtin_bit_cast(u16x2, w[0] & 0x7FFF7FFFu);
+      // magnitudes 0 .. 0x7C00 (infinity) raised to the top of 16 bits, where NaN
+      // wraps to the bottom: the maximum leaves NaN out, unless all are
+      constexpr unsigned short kUp = 0x83FF;
+      const u16x2 up = {kUp, kUp};
+      u16x2 m = __builtin_bit_cast(u16x2, w[0] & 0x7FFF7FFFu) + up;
 #pragma unroll
-      for (int j = 1; j < 4; ++j) m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, w[j] & 0x7FFF7FFFu));
-      const uint32_t mx = row_max(m[0] > m[1] ? m[0] : m[1]);
+      for (int j = 1; j < 4; ++j) m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, w[j] & 0x7FFF7FFFu) + up);
+      const uint32_t mx = (row_max(m[0] > m[1] ? m[0] : m[1]) - kUp) & 0xFFFFu;
       // s = fp16_rne(fp32(max|w|) / (2^(b_max-1) - 1))
       const uint16_t sb = f2h_rn(__fdiv_rn(h2f((uint16_t)mx), h - 1.0f));
       const float s = h2f(sb);
       if (c == 0) scales[(size_t)g * L.N + n0 + o] = sb;
-      quantise8(w, s, s == 0.0f ? 0.0f : __builtin_amdgcn_rcpf(s), h, q);
+      const bool in_range = s != 0.0f && sb != 0x7C00u;
+      quantise8(w, in_range ? s : 0.0f, in_range ? __builtin_amdgcn_rcpf(s) : 0.0f, h,
+                s == 0.0f ? h : 0.0f, q);
     } else {
       load_elems<ALIGNED, uint8_t, 8>((const uint8_t*)src + at, q);
     }

@@ -64,6 +64,29 @@ def test_pack_rounds_as_the_quotient(g, torch, levels):  # noqa: F811
     assert np.array_equal(_host(pc), orc.pack_codes_fast(q, desc.plane_bits, desc.tile_n, b_max))
 
 
+@pytest.mark.parametrize("levels", [(0, 2, 4, 8), (0, 2, 4, 6), (0, 2, 3, 4, 8), (0, 2, 4)])
+def test_pack_non_finite_weights(g, torch, levels):  # noqa: F811
+    # a NaN takes no part in its group's scale and gets code 0, as does an
+    # infinity; the finite weights beside an infinity get the code of zero
+    N, K, b_max = 512, 256, levels[-1]
+    half = 1 << (b_max - 1)
+    W = inputs.weights(N, K, 95).copy()
+    W[0, 3], W[1, 127], W[2, 5], W[3, 9:20] = np.nan, -np.nan, np.inf, -np.inf
+    W[4, 7], W[4, 8], W[5, 0:128], W[6, 1:128] = np.inf, np.nan, np.nan, np.nan
+    W[7, :128], W[7, 50], W[8, :128] = 0, np.nan, 65504.0
+    Wg = W.reshape(N, K // 128, 128).astype(np.float32)
+    amax = np.fmax.reduce(np.abs(Wg), axis=2)                # ignores NaN
+    with np.errstate(invalid="ignore", divide="ignore", over="ignore"):
+        s = (amax / np.float32(half - 1)).astype(np.float16)
+        r = np.rint(Wg / s.astype(np.float32)[:, :, None])
+        r = np.fmin(np.fmax(r, -half), half - 1)             # a NaN becomes -half
+        q = np.where(s[:, :, None] == 0, half, r + half).astype(np.uint8).reshape(N, K)
+    desc = g.grinqh_resolve_desc(g.make_desc(K, N, levels))
+    pc, ps = g.grinqh_pack(desc, W=_dev(torch, W))
+    assert np.array_equal(_host(ps), np.ascontiguousarray(s.T), equal_nan=True)
+    assert np.array_equal(_host(pc), orc.pack_codes_fast(q, desc.plane_bits, desc.tile_n, b_max))
+
+
 @pytest.mark.parametrize("S", [1, 7, 585, 1025])
 @pytest.mark.parametrize("levels", [(0, 8), (0, 2, 4, 6, 8), (0, 1, 2, 3, 4, 5, 6, 7, 8)])
 def test_calibrate_mean_stages(g, torch, S, levels):  # noqa: F811
