@@ -21,12 +21,16 @@
 // a row's slots at the paper's budgets, which idled before) and makes the
 // level the same in all lanes of a wave but at the list's level borders, so
 // a table's place in LDS is an immediate and the code's byte one operand.
-// Measured (us a call, levels {0,2,4,6,8} at 4 average bits, before / with the list,
-// the tables copied by LDS loads and the sums in registers): 4096 -> 6144 19.9 / 15.0,
-// 4096 -> 4096 15.2 / 11.6, 4096 -> 28672 60.2 / 53.4, 14336 -> 4096 34.4 / 31.2,
-// 1024 -> 1024 10.9 / 6.9; where every channel is at 8 bits nothing is left out and
-// the lookups' bank conflicts (random 512-byte tables) bound it: 4096 -> 6144 21.4 /
-// 22.1, 14336 -> 4096 51.0 / 48.1, two tokens of 1536 -> 10240 24.8 / 26.8.
+// The run's x and levels are loaded at once, a compile-time number per thread:
+// loads under conditions were waited for one by one, up to eight latencies.
+// Measured (us a call, levels {0,2,4,6,8} at 4 average bits; without the list /
+// with it, the tables copied by LDS loads and the sums in registers / with the
+// loads at once): 4096 -> 6144 19.3 / 14.8 / 13.7, 4096 -> 4096 15.1 / 11.6 / 10.8,
+// 4096 -> 28672 60.3 / 53.4 / 49.3, 14336 -> 4096 33.6 / 31.1 / 30.5, 1024 -> 1024 11.0 / 6.9 /
+// 6.3.  Where every channel is at 8 bits nothing is left out and the lookups' bank
+// conflicts (random 512-byte tables) bound it: 4096 -> 6144 22.0 / 22.6 / 22.0, 14336 ->
+// 4096 51.9 / 49.1 / 48.6, two tokens of 1536 -> 10240 25.0 / 26.7 / 25.1, of 1024 -> 28672
+// 41.1 / 44.5 / 42.0.
 #include <algorithm>
 #include <type_traits>
 
@@ -41,6 +45,7 @@ constexpr int kLutThreads = 256;
 constexpr int kStep = kLutThreads / 4;       // channel rows the workgroup looks up at once
 constexpr int kSub = 64;                     // outputs per workgroup
 constexpr int kMaxRun = 16 * 128;            // channels per workgroup (16 groups)
+static_assert(kMaxRun == 8 * kLutThreads, "the longest run's channels per thread");
 
 __global__ __launch_bounds__(kLutThreads) void k_zero_lut(float* __restrict__ y, long n) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -59,7 +64,8 @@ __device__ __forceinline__ float swap_add(float a, float b) {
   return __builtin_bit_cast(float, u) + __builtin_bit_cast(float, v);
 }
 
-template <int U>
+// MINE: channels per thread, kLutThreads MINE the longest run.
+template <int U, int MINE>
 __global__ __launch_bounds__(kLutThreads) void k_vmm_lut(const uint8_t* __restrict__ codes,
                                                         const uint16_t* __restrict__ luts,
                                                         const uint16_t* __restrict__ x,
@@ -69,7 +75,7 @@ __global__ __launch_bounds__(kLutThreads) void k_vmm_lut(const uint8_t* __restri
                                                         Thresholds th, uint8_t* __restrict__ lm_out) {
   extern __shared__ __align__(16) uint16_t s_lut[];          // [levels][kSub][2^b]
   __shared__ float s_red[kLutThreads / 64][kSub];
-  __shared__ uint32_t s_ent[kMaxRun];                         // active channels: x | row << 16 | level << 27
+  __shared__ uint32_t s_ent[MINE * kLutThreads];              // active channels: x | row << 16 | level << 27
   __shared__ __align__(16) int s_cnt[kMaxLevels][kLutThreads / 64];         // channels of a level in a wave's share
 
   // Work order: the K splits of a sub-tile, then the sub-tiles of a tile,
@@ -113,32 +119,34 @@ __global__ __launch_bounds__(kLutThreads) void k_vmm_lut(const uint8_t* __restri
   // sub-tile 0).  Then the active channels are listed by level: a wave ranks
   // its own channels of each level by ballot, and one exchange of the waves'
   // counts gives every level and wave its place.
-  constexpr int kMine = kMaxRun / kLutThreads;   // channels per thread, at most
-  uint32_t ent[kMine];
-  int rank[kMine];
+  uint32_t ent[MINE];
+  int rank[MINE];
   int cnt[kMaxLevels];
 #pragma unroll
   for (int l = 0; l < kMaxLevels; ++l) cnt[l] = 0;
-  uint16_t xs[kMine];
-  uint8_t ls[kMine];
+  // all loads before the first use: none under a condition (past the run the
+  // last channel again; without a level map x's bytes, unused)
+  uint32_t xs[MINE], ls[MINE];
+  const uint8_t* lmap = fused ? (const uint8_t*)x : lm;
 #pragma unroll
-  for (int m = 0; m < kMine; ++m) {              // all loads before the first use
-    if (m * kLutThreads >= nrows) break;         // the same in every thread
+  for (int m = 0; m < MINE; ++m) {
     const size_t k = (size_t)tok * L.K + kr0 + min(tid + m * kLutThreads, nrows - 1);
     xs[m] = x[k];
-    ls[m] = fused ? 0 : lm[k];
+    ls[m] = lmap[k];
   }
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int m = 0; m < kMine; ++m) {
+  for (int m = 0; m < MINE; ++m) asm volatile("" : "+v"(xs[m]), "+v"(ls[m]));   // (the compiler sinks them otherwise)
+#pragma unroll
+  for (int m = 0; m < MINE; ++m) {
     const int i = tid + m * kLutThreads;
     ent[m] = 0;
     rank[m] = 0;
-    if (m * kLutThreads >= nrows) continue;
     int lv = 0;
     if (i < nrows) {
-      const uint16_t xh = xs[m];
+      const uint32_t xh = xs[m];
       if (fused) {
-        const float ax = fabsf(h2f(xh));
+        const float ax = fabsf(h2f((uint16_t)xh));
 #pragma unroll
         for (int j = 0; j < kMaxLevels - 1; ++j)   // unused thresholds are +inf: no
           lv += ax >= th.theta[j] ? 1 : 0;         // branch, all loaded up front
@@ -147,7 +155,7 @@ __global__ __launch_bounds__(kLutThreads) void k_vmm_lut(const uint8_t* __restri
       } else {
         lv = min((int)ls[m], n_top);
       }
-      ent[m] = (uint32_t)xh | ((uint32_t)i << 16) | ((uint32_t)lv << 27);
+      ent[m] = xh | ((uint32_t)i << 16) | ((uint32_t)lv << 27);
     }
 #pragma unroll
     for (int l = 1; l < kMaxLevels; ++l) {
@@ -184,7 +192,7 @@ __global__ __launch_bounds__(kLutThreads) void k_vmm_lut(const uint8_t* __restri
       all += v;
     }
 #pragma unroll
-    for (int m = 0; m < kMine; ++m)
+    for (int m = 0; m < MINE; ++m)
       if ((int)(ent[m] >> 27) == l) s_ent[mine + rank[m]] = ent[m];
     n_ent += all;
     used_levels |= all ? 1u << l : 0u;
@@ -385,12 +393,12 @@ int lut_desc(const Layer& L, LutDesc* D) {
 // (sub-tile, token) pairs.  A workgroup costs its groups and about four more
 // (listing, table copy, sums), a CU the n workgroups that fall to it, and the
 // last one's length is added once, as nothing overlaps its end: n (g + 4) + g
-// is smallest at or within 5% of the best g of every shape swept.  Measured
-// (us at 4 average bits, levels {0,2,4,6,8}): 4096 -> 6144 14.9 with g = 4, 17.8
-// with 8; 4096 -> 4096 11.6 with 4, 13.4 with 8, 16.2 with 2; 14336 -> 4096 31.0
-// with 14 (two workgroups per CU), 33.7 with 16, 37.2 with 8; 1024 -> 1024 6.8
-// with 1, 9.5 with 4.  More than eight groups only where K is long: 4096 ->
-// 28672 53.1 with 8, 57.0 with 16 (two tokens 94.9 and 100.4).
+// is within 1.5% of the best g in the mean of 90 shapes and budgets swept (22% off
+// at worst, at 6 to 9 us).  Measured (us at 4 average bits, levels {0,2,4,6,8}):
+// 4096 -> 6144 13.8 with g = 4, 16.4 with 8; 4096 -> 4096 10.8 with 4, 13.0 with 8, 14.9
+// with 2; 14336 -> 4096 30.7 with 14 (two workgroups per CU), 33.4 with 16, 35.5 with
+// 8; 1024 -> 1024 6.3 with 1, 8.7 with 4.  More than eight groups only where K is long
+// (4096 -> 28672 49.3 with 8, 51.9 with 16; two tokens 90.7 and 92.8).
 static int groups_per_workgroup(int groups, long columns, int cus) {
   const int most = std::min(std::max(8, (groups + 3) / 4), std::min(groups, kMaxRun / kGroup));
   int best = 1;
@@ -427,14 +435,21 @@ int launch_vmm_lut(const Layer& L, const void* codes, const void* luts, const vo
   Thresholds none{};
   const Thresholds& tt = th ? *th : none;
   const int fused = th != nullptr;
-  if (L.u == 2)
-    hipLaunchKernelGGL(k_vmm_lut<2>, grid, dim3(kLutThreads), lds, s, (const uint8_t*)codes,
-                       (const uint16_t*)luts, (const uint16_t*)x, level_map, y, L, D, gps, (int)splits,
-                       fused, tt, level_map_out);
-  else
-    hipLaunchKernelGGL(k_vmm_lut<1>, grid, dim3(kLutThreads), lds, s, (const uint8_t*)codes,
-                       (const uint16_t*)luts, (const uint16_t*)x, level_map, y, L, D, gps, (int)splits,
-                       fused, tt, level_map_out);
+#define GRINQH_LUT(UU, MM)                                                                                    \
+  hipLaunchKernelGGL((k_vmm_lut<UU, MM>), grid, dim3(kLutThreads), lds, s, (const uint8_t*)codes,              \
+                     (const uint16_t*)luts, (const uint16_t*)x, level_map, y, L, D, gps, (int)splits, fused, \
+                     tt, level_map_out)
+  const int run = gps * kGroup;
+  if (L.u == 2) {
+    if (run <= 2 * kLutThreads) GRINQH_LUT(2, 2);
+    else if (run <= 4 * kLutThreads) GRINQH_LUT(2, 4);
+    else GRINQH_LUT(2, 8);
+  } else {
+    if (run <= 2 * kLutThreads) GRINQH_LUT(1, 2);
+    else if (run <= 4 * kLutThreads) GRINQH_LUT(1, 4);
+    else GRINQH_LUT(1, 8);
+  }
+#undef GRINQH_LUT
   return check_launch("vmm_lut");
 }
 

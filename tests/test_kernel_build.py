@@ -38,3 +38,19 @@ def test_decode_adds_are_one_instruction_each():
     columns = code.split("wait_copies(nlate")[1].split("float lost")[0]
     assert "add_to(yo" in columns and not re.search(r"\batomicAdd\b|__hip_atomic|unsafeAtomicAdd", columns)
     assert re.search(r'asm volatile\("global_atomic_add_f32 %0, %1, off"', code)
+
+
+def test_lut_channels_are_loaded_at_once(tmp_path):
+    # the run's x and level bytes all go out before the first wait
+    out = tmp_path / "lut.s"
+    r = subprocess.run([b.hipcc(), *b.HIPCC_FLAGS, *b.SOURCE_FLAGS.get("vmm_lut.hip", []), "--cuda-device-only", "-S",
+                        os.path.join(b.CSRC, "vmm_lut.hip"), "-o", str(out)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    kernels = re.split(r"\n(?=_ZN\S*k_vmm_lut\S*:)", out.read_text())[1:]
+    assert len(kernels) == 6
+    for k in kernels:
+        name, body = k.split("\n", 1)
+        prologue = body.split("s_barrier")[0]
+        before = re.split(r"s_waitcnt[^\n]*vmcnt", prologue)[0]
+        loads = r"global_load_u(?:short|byte)"
+        assert len(re.findall(loads, before)) == len(re.findall(loads, prologue)) >= 4, name
