@@ -398,9 +398,12 @@ int lut_desc(const Layer& L, LutDesc* D) {
 // 4096 -> 6144 13.8 with g = 4, 16.4 with 8; 4096 -> 4096 10.8 with 4, 13.0 with 8, 14.9
 // with 2; 14336 -> 4096 30.7 with 14 (two workgroups per CU), 33.4 with 16, 35.5 with
 // 8; 1024 -> 1024 6.3 with 1, 8.7 with 4.  More than eight groups only where K is long
-// (4096 -> 28672 49.3 with 8, 51.9 with 16; two tokens 90.7 and 92.8).
-static int groups_per_workgroup(int groups, long columns, int cus) {
-  const int most = std::min(std::max(8, (groups + 3) / 4), std::min(groups, kMaxRun / kGroup));
+// (4096 -> 28672 49.3 with 8, 51.9 with 16; two tokens 90.7 and 92.8), or with 1-bit
+// planes and more than two columns per CU (two tokens of 4096 -> 28672 139.5 with 8,
+// 132.7 with 16; one token, less than that, 72.1 and 75.4).
+static int groups_per_workgroup(int groups, long columns, int cus, int u) {
+  const int most = std::min(u == 1 && columns > 2 * cus ? 16 : std::max(8, (groups + 3) / 4),
+                            std::min(groups, kMaxRun / kGroup));
   int best = 1;
   long best_cost = 0;
   for (int g = 1; g <= most; ++g) {
@@ -427,7 +430,7 @@ int launch_vmm_lut(const Layer& L, const void* codes, const void* luts, const vo
     hipLaunchKernelGGL(k_zero_lut, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, y, n);
   }
   const long subtiles = (long)L.tiles * (L.T / kSub);
-  int gps = groups_per_workgroup(L.groups, subtiles * B, device_cus());
+  int gps = groups_per_workgroup(L.groups, subtiles * B, device_cus(), L.u);
   if (const int v = option(&Options::lut_groups)) gps = v <= L.groups ? v : L.groups;
   gps = gps > kMaxRun / kGroup ? kMaxRun / kGroup : gps;
   const long splits = (L.groups + gps - 1) / gps;
