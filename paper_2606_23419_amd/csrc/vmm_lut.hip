@@ -400,16 +400,23 @@ int lut_desc(const Layer& L, LutDesc* D) {
 // 8; 1024 -> 1024 6.3 with 1, 8.7 with 4.  More than eight groups only where K is long
 // (4096 -> 28672 49.3 with 8, 51.9 with 16; two tokens 90.7 and 92.8), or with 1-bit
 // planes and more than two columns per CU (two tokens of 4096 -> 28672 139.5 with 8,
-// 132.7 with 16; one token, less than that, 72.1 and 75.4).
-static int groups_per_workgroup(int groups, long columns, int cus, int u) {
-  const int most = std::min(u == 1 && columns > 2 * cus ? 16 : std::max(8, (groups + 3) / 4),
+// 132.7 with 16; one token, less than that, 72.1 and 75.4), or where the tables weigh
+// more: with a table of 8 bits (40 KB a copy) and at least 32 (column, group) units per
+// CU, so that up to sixteen groups still leave two workgroups per CU, the longer of
+// equal runs is taken, with 2-bit planes only up to 256 sub-tiles (beyond, 4096 -> 28672, two tokens at
+// 8 bits 146 with 8 and 156 with 16).  Four tokens of 4096 -> 4096 at 8 / 4 bits 39.9 /
+// 27.6 with 8, 34.8 / 24.4 with 16, with 1-bit planes 66.5 / 40.5 and 58.2 / 38.1.
+static int groups_per_workgroup(int groups, int subtiles, int B, int cus, int u, int entries) {
+  const long columns = (long)subtiles * B;
+  const bool heavy = entries >= 256 && columns * groups >= 32l * cus && (u == 1 || subtiles <= 256);
+  const int most = std::min(heavy || (u == 1 && columns > 2 * cus) ? 16 : std::max(8, (groups + 3) / 4),
                             std::min(groups, kMaxRun / kGroup));
   int best = 1;
   long best_cost = 0;
   for (int g = 1; g <= most; ++g) {
     const long splits = (groups + g - 1) / g;
     const long cost = (columns * splits + cus - 1) / cus * (g + 4) + g;
-    if (g == 1 || cost < best_cost) {
+    if (g == 1 || cost < best_cost || (heavy && cost == best_cost)) {
       best = g;
       best_cost = cost;
     }
@@ -430,7 +437,7 @@ int launch_vmm_lut(const Layer& L, const void* codes, const void* luts, const vo
     hipLaunchKernelGGL(k_zero_lut, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, y, n);
   }
   const long subtiles = (long)L.tiles * (L.T / kSub);
-  int gps = groups_per_workgroup(L.groups, subtiles * B, device_cus(), L.u);
+  int gps = groups_per_workgroup(L.groups, (int)subtiles, B, device_cus(), L.u, D.entries);
   if (const int v = option(&Options::lut_groups)) gps = v <= L.groups ? v : L.groups;
   gps = gps > kMaxRun / kGroup ? kMaxRun / kGroup : gps;
   const long splits = (L.groups + gps - 1) / gps;
