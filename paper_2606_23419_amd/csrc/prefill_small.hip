@@ -310,10 +310,11 @@ int launch_prefill_small(const Layer& L, const void* codes, const void* scales, 
   // more than a round of workgroups: two columns share one (82 against 94 us at
   // 4096 -> 28672, M = 77); at most half a round: K split in two (28 against 42 us at
   // 4096 -> 4096, M = 77 and 27 against 36 at M = 128; above, 4096 -> 6144 at M = 128 has 192
-  // workgroups of 256 CUs and took 51 split, 40 not)
+  // workgroups of 256 CUs and took 51 split, 40 not), but not where the first half's
+  // waves take all of K in one turn each (128 -> 8192, M = 80 8.9 split, 6.5 not)
   const int cus = device_cus();
   const int cw = wgs > cus ? 2 : 1;
-  const bool halves = wgs <= cus / 2;
+  const bool halves = wgs <= cus / 2 && L.K > kPsK * kPsWaves;
   const int split = halves && !accumulate ? 2 : 1;   // else one workgroup takes both halves in turn
   const dim3 grid((unsigned)(L.N / (kPsN * cw) * row_blocks), (unsigned)split);
   if (split == 2) {
