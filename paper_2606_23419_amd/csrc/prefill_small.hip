@@ -275,17 +275,28 @@ struct Blocks {
 // One block of tokens (M <= 80) while the workgroups of 128 outputs are a single
 // round of one per CU, or prefill.hip would take its narrower tiles: 32768
 // outputs on 256 CUs, M = 80, 4096 channels 68 us against 86, 33792 outputs 135
-// against 160.  Past that prefill.hip covers 256 outputs per CU and round, and
-// this kernel is still ahead
-//   - up to 48 tokens: 65536 outputs, M = 48: 1024 / 4096 channels 37 / 131 us
-//     against 41 / 147; 131072 outputs 71 / 264 against 82 / 295;
-//   - where its rounds are fewer than twice prefill.hip's, to 64 tokens or with
-//     rows under 8 bits: 81920 outputs, M = 64: 60 / 207 against 67 / 226, at 4 bits and
-//     M = 80 64 / 176 against 66 / 217; but at 8 bits and M = 80 68 / 236 against 68 / 227;
-//   - to 64 tokens where K is long: 65536 outputs, M = 64: 4096 channels 141 against
-//     147, 131072 outputs 287 against 303; but 1024 channels 43 against 42;
-// and not otherwise: M = 77..80: 65536 outputs, 1024 / 4096 channels 48 / 156 against
-// 42 / 146, 131072 outputs 92 / 316 against 85 / 298, 1-bit planes 59 / 186 against 53 / 177.
+// against 160; but not with 1-bit planes, M > 64 and a few turns per wave (28672 outputs, M
+// = 80: 512 / 1024 / 2048 channels 21.2 / 35.6 / 64 against 20.7 / 33.6 / 63).
+// Past that prefill.hip covers 256 outputs per CU and round.  To 32 tokens this
+// kernel is still ahead everywhere (65536 outputs, 512 channels, M = 32 24.9 against
+// 27.4).  With more tokens it is where it has enough turns of K to pipeline, the
+// more of them the more tokens, rounds and bytes a code has, as a share of
+// prefill.hip's time over 69632..98304 outputs (its rounds are fewer than twice
+// prefill.hip's), and over 40960 / 49152 / 57344 / 65536 outputs (twice):
+//   M    bits  channels  fewer        twice
+//   48   8     512       0.91..0.93   1.20 1.16 1.11 1.08
+//   48   8     2048      0.84         1.07 1.04 0.99 0.96
+//   48   8     4096      0.77..0.83   1.02 0.96 0.88 0.84
+//   48   4     1024      0.78         0.99 0.97 0.91 0.89
+//   48   8, 1-bit planes 2048  0.88   0.98 0.98 0.95 0.93   (1024: 0.95, 1.05)
+//   64   8     1024      0.95..0.98   (prefill.hip's)
+//   64   8     4096      0.84..0.92   1.13 1.03 0.96 0.92
+//   64   8, 1-bit planes 2048  0.97   4096: 1.01 1.01 0.97 0.94   (1024: 1.02)
+//   80   6     2048      1.02         (4096: 0.90..0.98)
+//   80   4     1024      1.01         (2048: 0.87..0.94)
+// and to 256 channels, where no wave has a second turn: 0.74 and 0.96 at M = 48, 0.84
+// at M = 64, 0.91 at M = 80 and fewer bits than 8.  M = 80 at 8 bits is prefill.hip's:
+// 65536 outputs, 1024 / 4096 channels 48 / 156 against 42 / 146.
 // More blocks as long as one workgroup per 64 outputs and block leaves a single
 // round on the chip: 4096 -> 4096 at M = 256 (256 workgroups) 39 us against 63,
 // 14336 -> 4096 111 against 211, 4096 -> 6144 at M = 128 (192) 40 against 65 but at
@@ -293,13 +304,24 @@ struct Blocks {
 bool prefill_small_takes(const Layer& L, int M) {
   if (M > 80 * 256) return false;
   const Blocks b(M);
-  const long cus = device_cus();
-  if (b.rows > 1) return (long)(L.N / kPsN) * b.rows <= cus;
-  const long rounds = (L.N / (2 * kPsN) + cus - 1) / cus;
-  if (rounds == 1 || !prefill_wide(L, M)) return true;
-  const long wide = (L.N / 256 + cus - 1) / cus;   // prefill.hip's
-  if (b.mt <= 3 || (b.mt == 4 && L.K >= 4096)) return true;
-  return rounds < 2 * wide && (b.mt == 4 || L.bmax < 8);
+  const long cus = device_cus(), pairs = L.N / (2 * kPsN);
+  if (b.rows > 1) return 2 * pairs * b.rows <= cus;
+  if (2 * pairs <= cus) return true;
+  const bool one_turn = L.K <= 256;
+  if (L.u == 1 && b.mt == 5 && !one_turn && L.K < 2048) return false;
+  const long rounds = (pairs + cus - 1) / cus;
+  if (rounds == 1 || b.mt <= 2 || !prefill_wide(L, M)) return true;
+  const bool light = L.u == 2 && L.bmax <= 4;
+  if (rounds < 2 * ((L.N / 256 + cus - 1) / cus)) {   // (prefill.hip's rounds)
+    if (b.mt == 3) return true;
+    if (b.mt == 4) return one_turn || L.K >= (L.u == 2 ? 1024 : 2048);
+    return L.bmax < 8 && (one_turn || L.K >= (light ? 2048 : 4096));
+  }
+  if (b.mt == 5) return false;
+  if (b.mt == 3 && one_turn) return true;
+  if (L.K < (b.mt == 4 ? 4096 : light ? 1024 : 2048)) return false;
+  // how full the last round is weighs where the codes weigh: a half or three quarters
+  return L.u == 1 || light || 4 * pairs >= (4 * rounds - (b.mt == 3 && L.K >= 4096 ? 2 : 1)) * cus;
 }
 
 int launch_prefill_small(const Layer& L, const void* codes, const void* scales, const void* x, int M, float* y,

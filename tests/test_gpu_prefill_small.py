@@ -77,7 +77,8 @@ def test_prefill_small_adds_what_it_would_store(g, torch, K, N, levels, M):  # n
 
 @pytest.mark.parametrize("levels,K,M,small", [
     ((0, 2, 4, 8), 256, 65, False), ((0, 2, 4, 8), 256, 49, False), ((0, 2, 3, 4, 8), 256, 80, False),
-    ((0, 2, 4, 8), 256, 48, True)])
+    ((0, 2, 4, 8), 256, 48, True), ((0, 2, 4, 8), 512, 33, False), ((0, 2, 3, 4, 8), 384, 48, False),
+    ((0, 2, 4, 8), 512, 32, True)])
 def test_prefill_small_leaves_a_second_round_to_the_wide_tiles(g, torch, opts, levels, K, M, small):  # noqa: F811
     # 256 outputs per CU: two rounds of 128-output workgroups, one of 256 x 256
     # tiles, whose sums come in another order
