@@ -141,7 +141,7 @@ struct MmArgs {
   float theta[kMaxLevels - 1];
 };
 
-template <int U, int W, int PL, int NB>
+template <int U, int W, int PL, int NB, bool FULL>
 struct MmShape {
   static constexpr int PBY = W * U / 8;              // bytes of one plane row of the W outputs
   static constexpr int CHK = PBY / 16;               // 16-byte chunks of it
@@ -157,10 +157,10 @@ struct MmShape {
   // Steps of a column that LDS holds at once, three workgroups per CU (at the
   // 4-bit budgets a list has 64 +- 6 rows of 2-bit planes, five steps).  The
   // first FIRST are multiplied while the others arrive; steps past SCAP then
-  // take their place.
+  // take their place.  FULL: all of them, for launches of two workgroups per CU.
   static constexpr int FIXED = COLS * COLB + 4 * 16 * MAXB * 2 + 2 * W + 16 * NB + 64;
   static constexpr int FIT = (160 * 1024 / 3 - FIXED) / (4 * BLKB);
-  static constexpr int SCAP = FIT > MAXB ? MAXB : FIT > MAXB / 2 ? FIT : MAXB / 2 + 1;
+  static constexpr int SCAP = FULL || FIT > MAXB ? MAXB : FIT > MAXB / 2 ? FIT : MAXB / 2 + 1;
   static constexpr int FIRST = (SCAP + 1) / 2 > MAXB - SCAP ? (SCAP + 1) / 2 : MAXB - SCAP;
   static constexpr int WB = 4 * SCAP * BLKB > RED ? 4 * SCAP * BLKB : RED;
   static_assert(FIRST < SCAP && FIRST >= 2, "LDS");
@@ -228,12 +228,12 @@ __device__ __forceinline__ void add_rests(const uint16_t* x, const uint8_t* rows
   lds_barrier();
 }
 
-template <int U, int W, int PL, int NB, bool TOPK>
+template <int U, int W, int PL, int NB, bool FULL, bool TOPK>
 __global__ __launch_bounds__(kMmThreads, 4) void k_vmm_mm(
     const uint16_t* __restrict__ x, const uint8_t* __restrict__ lm, int K, int fused, int run,
     int cols, const uint8_t* __restrict__ codes, const uint16_t* __restrict__ scales, float* __restrict__ y,
     uint8_t* __restrict__ lm_out, MmArgs A, TopkCuts tk) {
-  using S = MmShape<U, W, PL, NB>;
+  using S = MmShape<U, W, PL, NB, FULL>;
   constexpr int PBY = S::PBY, CHK = S::CHK, COLB = S::COLB, COLS = S::COLS, MAXB = S::MAXB;
   constexpr int OW = S::OW, OWP = S::OWP, NSL = S::NSL, NCB = S::NCB, BLKB = S::BLKB, SCAP = S::SCAP, FIRST = S::FIRST;
 
@@ -565,23 +565,35 @@ void launch_nb(int B, hipStream_t s, const void* codes, const void* scales, cons
   // Columns per workgroup: for one token the fewest that leave at most three
   // workgroups per CU (a further round of workgroups would start with the
   // latency of x again); for several, one (their digit sums weigh more).
-  const int cols = L.N / W;
+  const int cols = L.N / W, cus = device_cus();
   int run = 1;
-  while (B == 1 && run < cols && (long)((cols + run - 1) / run) * L.groups > 768) ++run;
+  while (B == 1 && run < cols && (long)((cols + run - 1) / run) * L.groups > 3 * cus) ++run;
   const dim3 grid((unsigned)((cols + run - 1) / run), (unsigned)L.groups);
-#define GRINQH_MM(NN, TK)                                                                        \
-  hipLaunchKernelGGL((k_vmm_mm<U, W, PL, NN, TK>), grid, dim3(kMmThreads), 0, s, (const uint16_t*)x, lm, \
+  // Longer runs that leave only two workgroups per CU have the LDS for every
+  // step of a column: no second pass at 6 and 8 bits (us at 4 / 6 / 8 bits, three workgroups' LDS
+  // and two's: 14336 -> 4096 9.9 / 13.3 / 14.3 and 9.9 / 11.7 / 13.5, 4096 -> 16384 10.2 / 14.0 / 16.7 and
+  // 10.0 / 12.2 / 15.3, 1-bit planes at 8 bits 20.9 and 17.3).  Not for one column, whose second
+  // pass comes while other workgroups of the CU multiply: 4096 -> 6144 at 8 bits 8.2 and 8.4, with 1-bit planes 9.9
+  // and 10.3; nor in place of a third workgroup: 8192 -> 10240 at 4 bits 12.5 and 14.5.
+  constexpr bool kSplit = MmShape<U, W, PL, 1, false>::SCAP < MmShape<U, W, PL, 1, false>::MAXB;
+  const bool full = kSplit && run > 1 && (long)grid.x * grid.y <= 2 * cus;
+#define GRINQH_MM(NN, FF, TK)                                                                    \
+  hipLaunchKernelGGL((k_vmm_mm<U, W, PL, NN, FF, TK>), grid, dim3(kMmThreads), 0, s, (const uint16_t*)x, lm, \
                      L.K, fused, run, cols, (const uint8_t*)codes, (const uint16_t*)scales, y, lm_out, A, tk)
   if (fused == 2) {
-    if constexpr (U == 2) GRINQH_MM(1, true);
+    if constexpr (U == 2) {
+      if (full) GRINQH_MM(1, kSplit, true);
+      else GRINQH_MM(1, false, true);
+    }
   } else if (B == 1) {
-    GRINQH_MM(1, false);
+    if (full) GRINQH_MM(1, kSplit, false);
+    else GRINQH_MM(1, false, false);
   } else if (B == 2) {
-    GRINQH_MM(2, false);
+    GRINQH_MM(2, false, false);
   } else if (B == 3) {
-    GRINQH_MM(3, false);
+    GRINQH_MM(3, false, false);
   } else {
-    GRINQH_MM(4, false);
+    GRINQH_MM(4, false, false);
   }
 #undef GRINQH_MM
 }

@@ -1,4 +1,6 @@
 """The matrix-core decode VMM at the edges of its lists, passes and columns."""
+import types
+
 import numpy as np
 import pytest
 
@@ -57,21 +59,34 @@ def test_vmm_mm_lists(g, torch, kind, K, N, levels, tile_n, B):  # noqa: F811
     assert np.all(err <= _bound(L, x, lm, L.desc.plane_bits)), (err.max(), np.abs(ref).max())
 
 
-def test_vmm_mm_columns_per_workgroup(g, torch):  # noqa: F811
-    # 2 x 896 columns of 256 outputs and one group: 2 and 3 columns per workgroup,
-    # the last workgroup with fewer
-    for N in (2 * 896 * 256, 1537 * 256):
-        K, levels = 128, (0, 2, 4, 8)
-        L = Layer(g, torch, K, N, levels, cfg=91, tile_n=256, codes_src=True)
-        g.grinqh_set_option(g.GRINQH_OPT_GROUPS_PER_WG, 1)
-        try:
-            x = inputs.activations_t3(K, 1, 91)
-            lm = _maps("random", 1, K, 3, 91)
-            y = g.grinqh_vmm(L.desc, L.pc, L.ps, _dev(torch, x), _dev(torch, lm))
-        finally:
-            g.grinqh_set_option(g.GRINQH_OPT_GROUPS_PER_WG, 0)
-        ref = orc.vmm_batch(L.codes, L.scales, x, lm, levels)
-        assert np.all(np.abs(_host(y) - ref) <= _bound(L, x, lm, 2))
+@pytest.mark.parametrize("K,N,levels,tile_n,run,full", [
+    (128, 1536 * 256, (0, 2, 4, 8), 256, 2, False), (128, 1537 * 256, (0, 2, 4, 8), 256, 3, False),
+    (1024, 97 * 512, (0, 2, 4, 6, 8), 512, 2, True), (1024, 98 * 512, (0, 2, 4, 6), 1024, 2, True),
+    (512, 259 * 512, (0, 2, 4, 6, 8), 512, 2, False), (1024, 97 * 512, (0, 2, 4), 512, 2, True),
+    (1024, 97 * 512, (0, 2, 3, 4, 8), 512, 2, True), (512, 259 * 512, (0, 2, 3, 4, 8), 512, 2, False),
+    (1152, 88 * 512, (0, 2, 3, 4, 8), 1024, 2, True)])
+def test_vmm_mm_columns_per_workgroup(g, torch, opts, K, N, levels, tile_n, run, full):  # noqa: F811
+    # several columns per workgroup, the last workgroup with fewer where their
+    # number leaves a remainder; a second pass over a column (512 outputs, full
+    # depth) or LDS for all of it (at most two workgroups per CU).  `run` and
+    # `full` are the launcher's rule for 256 CUs, stated here again.
+    width, groups = min(tile_n, 512), K // 128
+    cols, r = N // width, 1
+    while -(-cols // r) * groups > 3 * 256:
+        r += 1
+    assert r == run and (-(-cols // r) * groups <= 2 * 256) == full
+    L = Layer(g, torch, K, N, levels, cfg=91, tile_n=tile_n, codes_src=True)
+    opts(g.GRINQH_OPT_GROUPS_PER_WG, 1)       # this kernel, whatever the layer's size
+    x = inputs.activations_t3(K, 1, 91)
+    idx = np.unique(np.concatenate([np.arange(0, N, 37), np.arange(N - width, N)]))   # some of every column
+    part = types.SimpleNamespace(K=K, b_max=L.b_max, scales=np.ascontiguousarray(L.scales[:, idx]))
+    codes = np.ascontiguousarray(L.codes[idx])
+    for kind in ("full", "uneven", "random", "empty"):
+        lm = _maps(kind, 1, K, len(levels) - 1, 91)
+        y = _host(g.grinqh_vmm(L.desc, L.pc, L.ps, _dev(torch, x), _dev(torch, lm)))[:, idx]
+        ref = orc.vmm_batch(codes, part.scales, x, lm, levels)
+        err, bound = np.abs(y - ref), _bound(part, x, lm, L.desc.plane_bits)
+        assert np.all(err <= bound), (kind, np.max(err / np.maximum(bound, 1e-300)))
 
 
 @pytest.mark.parametrize("levels,B", [((0, 2, 4, 6, 8), 1), ((0, 2, 4, 6, 8), 3), ((0, 2, 3, 4, 8), 2)])
