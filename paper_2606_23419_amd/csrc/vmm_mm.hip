@@ -51,6 +51,10 @@
 // add_rests costs such a workgroup some microseconds.  No group needs it where
 // the smallest activations are skipped (Student-t and SwiGLU x, 20% at level 0);
 // with every channel active 0.01% of the groups do (0.06% with 1-bit planes).
+// Finding out costs each launch about 0.1 us (4096 -> 6144 at 2 bits 4.9 -> 5.05), with every
+// channel active up to 0.5 (two tokens at 8 bits 8.1 -> 8.7).  What it keeps lies in masks and in the B columns'
+// pads: as bytes of LDS it cost b_max 4, four tokens a workgroup per CU (14336 -> 4096
+// 12.1 -> 14.8 us, now 12.0).
 //
 // Per group and output y_n += s_{g,n} (sum_k X_k t_k 2^-s + beta_g), t_k the
 // code truncated to the channel's level (8-bit units), beta_g = sum over
@@ -149,6 +153,7 @@ struct MmShape {
   static constexpr int MAXB = 2 * PL;                // blocks of a list, steps of a column at most
   static constexpr int COLS = 4 * NB;                // B columns: four digits per token
   static constexpr int COLB = MAXB * 64 + 16;        // bytes of one B column (padded)
+  static constexpr int LEFT = MAXB * 64;             // in the pad of column j: what list j leaves of each token's x
   static constexpr int OW = W / 8;                   // outputs per wave
   static constexpr int OWP = OW + 4;
   static constexpr int NSL = 4 / U;                  // outputs per nibble
@@ -158,7 +163,7 @@ struct MmShape {
   // 4-bit budgets a list has 64 +- 6 rows of 2-bit planes, five steps).  The
   // first FIRST are multiplied while the others arrive; steps past SCAP then
   // take their place.  FULL: all of them, for launches of two workgroups per CU.
-  static constexpr int FIXED = COLS * COLB + 4 * 16 * MAXB * 2 + 2 * W + 16 * NB + 64;
+  static constexpr int FIXED = COLS * COLB + 4 * 16 * MAXB * 2 + 2 * W + 16 * NB + 16 * PL * NB + 64;
   static constexpr int FIT = (160 * 1024 / 3 - FIXED) / (4 * BLKB);
   static constexpr int SCAP = FULL || FIT > MAXB ? MAXB : FIT > MAXB / 2 ? FIT : MAXB / 2 + 1;
   static constexpr int FIRST = (SCAP + 1) / 2 > MAXB - SCAP ? (SCAP + 1) / 2 : MAXB - SCAP;
@@ -186,14 +191,17 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 constexpr float kRestMax = 2.0f;         // units of X
+constexpr float kRestList = 0.25f;       // what a list may leave in any case
+constexpr int kMuchLeft = 1 << 16;       // in a list's number of blocks: it leaves more than a quarter of that
 
 // What rounding to X left of x, for one token and the W outputs from n0 on:
 //   y_n += s_n sum_k rest_k (t_k + phi_b - 128) unit,  rest_k = x_k to_fix - X_k
-// in units of X.  depth: planes read per channel (0: none), valid in lists with
-// left > 0.  All threads call it, after a barrier; sum: W floats of LDS.
+// in units of X.  deeper[j][p]: the channels of list j read to more than p planes,
+// valid in lists with left > kRestList (the others' rests stay out).  All threads call it, after a barrier; sum: W floats of LDS.
 template <int U, int W, int PL>
 __device__ __forceinline__ void add_rests(const uint16_t* x, const uint8_t* rows, const uint16_t* scales, float* y,
-                                          const uint8_t* depth, const float* left, int left_stride, float* sum, float to_fix,
+                                          const uint32_t* deeper, const float* left, int left_stride, float* sum,
+                                          float to_fix,
                                           float unit, int RB, int plane_bytes, int bmax) {
   constexpr int CW = W / 16;               // 16 outputs per thread, 16 or 32 rows at once
   const int tid = threadIdx.x, o0 = 16 * (tid % CW);
@@ -205,7 +213,10 @@ __device__ __forceinline__ void add_rests(const uint16_t* x, const uint8_t* rows
 #pragma unroll 1
   for (int r = tid / CW; r < kGroup; r += kMmThreads / CW) {
     const float fix = h2f(x[r]) * to_fix, rest = fix - rintf(fix);
-    const int d = left[(r >> 5) * left_stride] > 0.0f && rest != 0.0f ? depth[r] : 0;
+    int d = 0;
+    if (left[(r >> 5) * left_stride] > kRestList && rest != 0.0f)
+#pragma unroll
+      for (int p = 0; p < PL; ++p) d += (int)(deeper[(r >> 5) * PL + p] >> (r & 31)) & 1;
     const uint8_t* row = rows + (size_t)r * RB + o0 * U / 8;
     uint32_t m[PL], c[4], q[4];            // planes; 2-bit fields; codes: byte i of q[j] is output 4 i + j
 #pragma unroll
@@ -243,8 +254,11 @@ __global__ __launch_bounds__(kMmThreads, 4) void k_vmm_mm(
   __shared__ __align__(16) uint16_t s_list[4][16][MAXB];   // row offsets / 64: row r of block b at [r][b]
   __shared__ __align__(16) float s_beta[NB][4];
   __shared__ __align__(16) int s_nblk[4];
-  __shared__ __align__(16) float s_left[4][NB == 3 ? 4 : NB];   // per list: sum of |x to_fix - X|
-  __shared__ __align__(16) uint8_t s_depth[NB][kGroup];    // where that is not zero
+  __shared__ __align__(16) uint32_t s_deeper[NB][4][PL];   // lists that leave something: the channels deeper than p planes
+  static_assert(!(U == 2 && PL == 2) ||
+                    sizeof(s_w) + sizeof(s_scale) + sizeof(s_b) + sizeof(s_list) + sizeof(s_beta) + sizeof(s_nblk) +
+                            sizeof(s_deeper) <= 160 * 1024 / 4,
+                "four workgroups per CU where rows have two planes");
   static_assert(!TOPK || sizeof(topksel::Scratch) <= sizeof(s_w), "the selection's scratch lies over the weights' place");
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -311,7 +325,6 @@ __global__ __launch_bounds__(kMmThreads, 4) void k_vmm_mm(
       const int p = 2 * j + half, sl = slot0 + p;
       if (p < du) s_list[list][sl & 15][sl >> 4] = (uint16_t)(row + p * pstep);
     }
-    if (lane == 0) s_nblk[list] = nblk;
   }
   wave_lds_order();
 
@@ -382,15 +395,6 @@ __global__ __launch_bounds__(kMmThreads, 4) void k_vmm_mm(
     const float fx = h2f((uint16_t)xc[t]);
     const float Xf = rintf(fx * to_fix);
     const int X = cvt_i32(Xf);
-    if (sub == 0) {
-      // fx * 0 carries an infinite or NaN x of an active channel into every output
-      const float phi = phi_minus_offset(U * d[t], bmax);
-      const float unfix = __builtin_bit_cast(float, (127u - FIX + e_max[t]) << 23);
-      const float beta = half_sum_dpp(d[t] ? fmaf(Xf * unfix, phi, fx * 0.0f) : 0.0f);
-      if (lane == 0) s_beta[t][list] = beta;
-      rest[t] = d[t] ? fabsf(fx * to_fix - Xf) : 0.0f;
-      most = fmaxf(most, rest[t]);
-    }
     // the list's half waves take its planes in turn
 #pragma unroll
     for (int j = 0; j < (PL + 3) / 4; ++j) {
@@ -405,20 +409,44 @@ __global__ __launch_bounds__(kMmThreads, 4) void k_vmm_mm(
         store_digits<COLB>(lds_addr(s_b) + (uint32_t)(4 * t * COLB + 16 * list + pos), dg);
       }
     }
+    if (sub == 0) {
+      // fx * 0 carries an infinite or NaN x of an active channel into every output
+      const float phi = phi_minus_offset(U * d[t], bmax);
+      const float unfix = __builtin_bit_cast(float, (127u - FIX + e_max[t]) << 23);
+      const float beta = half_sum_dpp(d[t] ? fmaf(Xf * unfix, phi, fx * 0.0f) : 0.0f);
+      if (lane == 0) s_beta[t][list] = beta;
+      rest[t] = d[t] ? fabsf(fx * to_fix - Xf) : 0.0f;
+      most = fmaxf(most, rest[t]);
+    }
   }
 
   if (sub == 0) {
     float left[NB];
+    bool much = false;                     // the four lists can be past kRestMax together
 #pragma unroll
     for (int t = 0; t < NB; ++t) left[t] = 0.0f;
-    if (__builtin_expect(__ballot(most > 0.0f) != 0, 0)) {
+    if (__builtin_expect(__ballot(most > kRestList / 32) != 0, 0)) {
+      bool some = false;
 #pragma unroll
       for (int t = 0; t < NB; ++t) {
         left[t] = half_sum_dpp(rest[t]);
-        if (half == 0) s_depth[t][ch] = (uint8_t)d[t];
+        some |= left[t] > kRestList;
+        much |= left[t] > kRestMax / 4;
+      }
+      if (__ballot(some) != 0) {
+#pragma unroll
+        for (int t = 0; t < NB; ++t)
+#pragma unroll
+          for (int p = 0; p < PL; ++p) {
+            const uint32_t deeper = (uint32_t)__ballot(d[t] > p);
+            if (lane == 0) s_deeper[t][list][p] = deeper;
+          }
       }
     }
-    if (lane == 0) __builtin_memcpy(s_left[list], left, sizeof(left));
+    if (lane == 0) {
+      __builtin_memcpy(&s_b[list * COLB + S::LEFT], left, sizeof(left));
+      s_nblk[list] = nblk | (much ? kMuchLeft : 0);
+    }
   }
 
   // ---- the columns
@@ -435,13 +463,16 @@ __global__ __launch_bounds__(kMmThreads, 4) void k_vmm_mm(
   const int rcb = o / (16 * NSL), ri = (o / NSL) % 16, re = o % NSL;
   const float s_e = __builtin_bit_cast(float, (uint32_t)(127 - re * U) << 23);   // 2^(-e U)
 
+  int rests = 0;
   for (int col = 0; col < ncol; ++col) {
     // the first blocks of every list (behind the copies: the last column's adds,
     // one instruction per token; no wave skips one, half its lanes take part at least)
     wait_copies(nlate + (col ? NB : 0));
     lds_barrier();
     const int4 nb4 = *(const int4*)&s_nblk[0];
-    const int steps = __builtin_amdgcn_readfirstlane(max(max(nb4.x, nb4.y), max(nb4.z, nb4.w)));
+    const int steps = __builtin_amdgcn_readfirstlane(
+        max(max(nb4.x & (kMuchLeft - 1), nb4.y & (kMuchLeft - 1)), max(nb4.z & (kMuchLeft - 1), nb4.w & (kMuchLeft - 1))));
+    rests = __builtin_amdgcn_readfirstlane(nb4.x | nb4.y | nb4.z | nb4.w) & kMuchLeft;
     v4i acc[NCB][NSL];
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb)
@@ -525,13 +556,16 @@ __global__ __launch_bounds__(kMmThreads, 4) void k_vmm_mm(
   }
 
   // ---- groups whose x is not exact enough
-  float lost[NB];                          // (a token with an active infinity or NaN: NaN, left out)
+  if (__builtin_expect(rests != 0, 0)) {
+    float worst = 0.0f;                    // (a token with an active infinity or NaN: NaN, left out)
 #pragma unroll
-  for (int t = 0; t < NB; ++t) lost[t] = (s_left[0][t] + s_left[1][t]) + (s_left[2][t] + s_left[3][t]);
-  float worst = lost[0];
+    for (int t = 0; t < NB; ++t) {
+      float lost = 0.0f;
 #pragma unroll
-  for (int t = 1; t < NB; ++t) worst = fmaxf(worst, lost[t]);
-  if (__builtin_expect(worst > kRestMax, 0)) {
+      for (int j = 0; j < 4; ++j) lost += *(const float*)&s_b[j * COLB + S::LEFT + 4 * t];
+      worst = fmaxf(worst, lost);
+    }
+    if (!(worst > kRestMax)) return;
     lds_barrier();                         // the digit sums are read: their place is free
 #pragma unroll 1
     for (int i = 0; i < ncol * NB; ++i) {
@@ -540,9 +574,8 @@ __global__ __launch_bounds__(kMmThreads, 4) void k_vmm_mm(
 #pragma unroll
       for (int j = 1; j < NB; ++j) e = t == j ? e_max[j] : e;
       add_rests<U, W, PL>(x + (size_t)t * K + k0, codes + ((size_t)tile * K + k0) * RB + ob,
-                          scales + (size_t)blockIdx.y * N + n0, y + (size_t)t * N + n0, s_depth[t], &s_left[0][t],
-                          (int)(sizeof(s_left[0]) / 4),
-                          (float*)s_w, __builtin_bit_cast(float, (127u + FIX - e) << 23),
+                          scales + (size_t)blockIdx.y * N + n0, y + (size_t)t * N + n0, &s_deeper[t][0][0],
+                          (const float*)&s_b[S::LEFT + 4 * t], COLB / 4, (float*)s_w, __builtin_bit_cast(float, (127u + FIX - e) << 23),
                           __builtin_bit_cast(float, (127u - FIX + e) << 23) * A.sfac, RB, T * U / 8, bmax);
     }
   }
