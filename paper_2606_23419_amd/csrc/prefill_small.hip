@@ -289,14 +289,16 @@ struct Blocks {
 //   48   8     4096      0.77..0.83   1.02 0.96 0.88 0.84
 //   48   4     1024      0.78         0.99 0.97 0.91 0.89
 //   48   8, 1-bit planes 2048  0.88   0.98 0.98 0.95 0.93   (1024: 0.95, 1.05)
-//   64   8     1024      0.95..0.98   (prefill.hip's)
-//   64   8     4096      0.84..0.92   1.13 1.03 0.96 0.92
-//   64   8, 1-bit planes 2048  0.97   4096: 1.01 1.01 0.97 0.94   (1024: 1.02)
-//   80   6     2048      1.02         (4096: 0.90..0.98)
-//   80   4     1024      1.01         (2048: 0.87..0.94)
-// and to 256 channels, where no wave has a second turn: 0.74 and 0.96 at M = 48, 0.84
-// at M = 64, 0.91 at M = 80 and fewer bits than 8.  M = 80 at 8 bits is prefill.hip's:
-// 65536 outputs, 1024 / 4096 channels 48 / 156 against 42 / 146.
+//   64   8     1024      0.96..0.99   1.25 1.21 1.13 1.11   (512: 1.05)
+//   64   8     4096      0.84..0.92   1.14 1.04 0.97 0.93
+//   64   8, 1-bit planes 2048  0.97   1.06 1.07 1.04 1.02   (1024: 1.02; 4096: 1.00 1.00 0.97 0.94)
+//   64   4     2048      0.81..0.84   1.04 1.02 0.95 0.89
+//   80   6     4096      0.92..1.00   1.23 1.13 1.04 0.97   (2048: 1.04)
+//   80   4     4096      0.81..0.89   1.11 1.04 0.94 0.89   (2048: 0.87..0.95, 1024: 1.01)
+// and to 256 channels, where no wave has a second turn: fewer rounds 0.70..0.96, twice 0.87..0.98
+// at M = 48, at M = 64 only with 1-bit planes 0.90..0.95 (1.00..1.06 with 2-bit ones).
+// M = 80 at 8 bits is prefill.hip's: 65536 outputs, 1024 / 4096 channels 48 / 156 against
+// 42 / 146.
 // More blocks as long as one workgroup per 64 outputs and block leaves a single
 // round on the chip: 4096 -> 4096 at M = 256 (256 workgroups) 39 us against 63,
 // 14336 -> 4096 111 against 211, 4096 -> 6144 at M = 128 (192) 40 against 65 but at
@@ -313,15 +315,15 @@ bool prefill_small_takes(const Layer& L, int M) {
   if (rounds == 1 || b.mt <= 2 || !prefill_wide(L, M)) return true;
   const bool light = L.u == 2 && L.bmax <= 4;
   if (rounds < 2 * ((L.N / 256 + cus - 1) / cus)) {   // (prefill.hip's rounds)
-    if (b.mt == 3) return true;
-    if (b.mt == 4) return one_turn || L.K >= (L.u == 2 ? 1024 : 2048);
-    return L.bmax < 8 && (one_turn || L.K >= (light ? 2048 : 4096));
+    if (one_turn || b.mt == 3) return true;
+    if (b.mt == 4) return L.K >= (L.u == 2 ? 1024 : 2048);
+    return L.bmax < 8 && L.K >= (light ? 2048 : 4096);
   }
-  if (b.mt == 5) return false;
-  if (b.mt == 3 && one_turn) return true;
-  if (L.K < (b.mt == 4 ? 4096 : light ? 1024 : 2048)) return false;
-  // how full the last round is weighs where the codes weigh: a half or three quarters
-  return L.u == 1 || light || 4 * pairs >= (4 * rounds - (b.mt == 3 && L.K >= 4096 ? 2 : 1)) * cus;
+  if (one_turn) return b.mt == 3 || (b.mt == 4 && L.u == 1);
+  const long quarters = 4 * (pairs - (rounds - 1) * cus) / cus;   // of the last round
+  if (light) return L.K >= (b.mt == 3 ? 1024 : b.mt == 4 && quarters >= 3 ? 2048 : 4096) && (b.mt < 5 || quarters >= 3);
+  if (b.mt == 5 || L.K < (b.mt == 3 ? 2048 : 4096)) return false;
+  return L.u == 1 || quarters >= (b.mt == 3 && L.K >= 4096 ? 2 : 3);
 }
 
 int launch_prefill_small(const Layer& L, const void* codes, const void* scales, const void* x, int M, float* y,
