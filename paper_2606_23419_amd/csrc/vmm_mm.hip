@@ -51,10 +51,10 @@
 // add_rests costs such a workgroup some microseconds.  No group needs it where
 // the smallest activations are skipped (Student-t and SwiGLU x, 20% at level 0);
 // with every channel active 0.01% of the groups do (0.06% with 1-bit planes).
-// Finding out costs each launch about 0.1 us (4096 -> 6144 at 2 bits 4.9 -> 5.05), with every
-// channel active up to 0.5 (two tokens at 8 bits 8.1 -> 8.7).  What it keeps lies in masks and in the B columns'
-// pads: as bytes of LDS it cost b_max 4, four tokens a workgroup per CU (14336 -> 4096
-// 12.1 -> 14.8 us, now 12.0).
+// Having it costs the others little: 4096 -> 6144 at 2 bits 4.96 -> 5.09 us, at 4 bits 6.17 ->
+// 6.21, four tokens 8.92 -> 9.06, two tokens at 8 bits 8.20 -> 8.84 (the most seen).  What
+// it needs lies in masks and in the B columns' pads: as bytes of LDS it took a workgroup
+// from each CU at b_max 4 and four tokens (14336 -> 4096 12.1 -> 14.8 us, now 12.0).
 //
 // Per group and output y_n += s_{g,n} (sum_k X_k t_k 2^-s + beta_g), t_k the
 // code truncated to the channel's level (8-bit units), beta_g = sum over

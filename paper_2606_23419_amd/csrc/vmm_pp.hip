@@ -408,7 +408,7 @@ bool vmm_pp_supported(const Layer& L, int B) {
 bool vmm_pp_takes(const Layer& L, int B) {
   if (!vmm_pp_supported(L, B)) return false;
   if (const int v = option(&Options::groups_per_wg)) return v >= 2;
-  return (long)L.tiles * L.groups >= 768;
+  return (long)L.tiles * L.groups >= 3 * device_cus();
 }
 
 int launch_vmm_pp(const Layer& L, const void* codes, const void* scales, const void* x,
