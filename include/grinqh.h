@@ -279,9 +279,12 @@ GRINQH_API int grinqh_vmm_lut_threshold(const grinqh_layer_desc* desc, const voi
  * process-wide overrides of launch choices that never change results beyond
  * rounding order.  Value 0 restores each launcher's own choice.
  *   GRINQH_OPT_VMM_KERNEL: GRINQH_KERNEL_PER_PLANE or GRINQH_KERNEL_GENERAL
- *     runs that kernel for B = 1 too (the batch kernels otherwise).
- *   GRINQH_OPT_GROUPS_PER_WG: 1..4 groups of 128 channels per workgroup
- *     (kernels that take fewer use their maximum).
+ *     runs that kernel (grinqh_vmm, grinqh_vmm_threshold, any B) in place of
+ *     the default ones.
+ *   GRINQH_OPT_GROUPS_PER_WG: chooses between the two default kernels at B = 1
+ *     and 2-bit planes: 1 the matrix-core kernel (one group of 128 channels per
+ *     workgroup), 2..4 the register kernel (two groups).  The per-plane kernel
+ *     takes that many groups per workgroup, or its maximum if that is less.
  *   GRINQH_OPT_PREFILL_TILE: 1, 2, 3 = 256x256, 256x128, 128x128 prefill tiles.
  *   GRINQH_OPT_LUT_GROUPS: 1..16 groups per workgroup of the LUT VMM.
  *   GRINQH_OPT_PREFILL_CUS: 1..4096, the CU count the prefill balances its

@@ -75,8 +75,8 @@ __device__ __forceinline__ uint16_t f2h_rn(float f) {
 // Launch overrides set through grinqh_set_option (tests and measurements);
 // 0 everywhere means each launcher's own choice.  Read with relaxed loads.
 struct Options {
-  int vmm_kernel;       // GRINQH_KERNEL_*: the batch-1 kernel
-  int groups_per_wg;    // groups of 128 channels per workgroup, where a kernel allows it
+  int vmm_kernel;       // GRINQH_KERNEL_*: the VMM kernel
+  int groups_per_wg;    // which batch-1 kernel; groups per workgroup of the per-plane one
   int prefill_tile;     // 1..3: 256x256, 256x128, 128x128
   int lut_groups;       // groups per workgroup of the LUT VMM
   int prefill_cus;      // CUs the prefill counts its rounds in (0: the device's)

@@ -398,16 +398,30 @@ bool vmm_pp_supported(const Layer& L, int B) {
          (long long)L.K * L.RB < (1ll << 31);
 }
 
-// The layers this kernel takes at batch 1: from 768 (tile, group) units on
-// (merged gate|up 4096 -> 28672: 896), two groups per workgroup.  There it
-// streams 256-byte plane rows and adds half as many partial sums; against it
-// k_vmm_mm took 15.9 against 15.6 us at 4 bits and 26.1 against 22.8 at 8
-// (11.3 against 12.2 at 2 bits, which the launcher can't tell).  Below, k_vmm_mm:
-// down 14336 -> 4096 (448 units) 9.6 against 10.2 us at 4 bits, 13.6 against 13.6
-// at 8, qkv 4096 -> 6144 (384) 6.0 against 7.7.
+// The layers this kernel takes at batch 1: wide ones from three (tile, group)
+// units per CU on, two groups per workgroup.  There it streams whole plane rows
+// and adds half as many partial sums, and needs no second pass at full depth.  us
+// with this kernel / with k_vmm_mm at 2, 4, 6 and 8 bits of 8 on 256 CUs:
+//   tiles of 1024, 896 units   4096 -> 28672    12.7/11.9 16.2/16.8 19.7/22.8 23.9/28.1
+//                  896         28672 -> 4096    12.5/14.3 16.0/18.0 19.6/21.9 23.2/25.2
+//                  1024        8192 -> 16384    12.7/12.4 16.9/17.0 20.7/23.6 25.3/29.8
+//                  4096        4096 -> 131072   36.4/34.3 53.1/55.1 69.1/76.2 89.1/94.2
+//   and behind where k_vmm_mm's workgroups come out at three per CU:
+//                  768         4096 -> 24576    12.8/10.2 16.6/14.7 18.6/18.8 21.5/23.0
+//                  1080        5120 -> 27648    15.3/12.7 21.0/17.7 25.9/24.1 31.0/28.7
+//   (at b_max 6 and 4 within 10% either way: 896 units 15.9/16.2 at 4 bits of 6, 13.3/13.4 at
+//   3 of 4, 4096 units 52.4/54.7 and 40.9/43.3; 768 15.7/13.8 and 13.2/11.1);
+//   tiles of 512, 3584 units   8192 -> 28672    22.7/18.1 29.9/26.7 35.5/36.7 42.3/46.2
+//   but with fewer planes a row k_vmm_mm is ahead: 29.9/26.6 at 4 bits of 6, 24.6/21.2 at 3 of 4;
+//   tiles of 256 are k_vmm_mm's: 7168 units 8192 -> 28672 31.3/24.4 40.6/32.8 44.8/39.1 49.5/45.6,
+//   1024 units 4096 -> 8192 7.5/6.4 9.2/7.7 10.2/8.9 11.9/10.0.
+// Below three units per CU k_vmm_mm: 704 units 4096 -> 22528 12.1/9.4 15.4/13.3 17.4/17.7
+// 20.6/21.8, 448 units 14336 -> 4096 (one group per workgroup here) 8.9/8.1 11.0/9.9 12.1/11.6
+// 13.7/13.0.  (The launcher can't tell the bits of a call.)
 bool vmm_pp_takes(const Layer& L, int B) {
   if (!vmm_pp_supported(L, B)) return false;
   if (const int v = option(&Options::groups_per_wg)) return v >= 2;
+  if (L.T == 256 || (L.T == 512 && L.P < 4)) return false;
   return (long)L.tiles * L.groups >= 3 * device_cus();
 }
 

@@ -155,3 +155,24 @@ def test_vmm_mm_wide_range_in_a_group(g, torch, K, N, levels, tile_n, B, small, 
     err = np.abs(_host(y) - ref)
     bound = _bound(L, x, lm, L.desc.plane_bits)
     assert np.all(err <= bound), (np.max(err / bound), np.abs(ref).max())
+
+
+@pytest.mark.parametrize("tile_n,levels,units,mm", [
+    (256, (0, 2, 4, 8), 768, True), (512, (0, 2, 4, 6), 768, True), (512, (0, 2, 4), 768, True),
+    (512, (0, 2, 4, 8), 768, False), (1024, (0, 2, 4, 6), 768, False), (1024, (0, 2, 4, 8), 767, True)])
+def test_batch1_kernel_by_size(g, torch, opts, tile_n, levels, units, mm):  # noqa: F811
+    # one group, so one add per output: the two kernels' sums are told apart by
+    # their bits (`units` for 256 CUs)
+    K, N = 128, units * tile_n
+    L = Layer(g, torch, K, N, levels, cfg=101, tile_n=tile_n, codes_src=True)
+    x, lm = inputs.activations_t3(K, 1, 101), _maps("random", 1, K, len(levels) - 1, 101)
+
+    def call(force):
+        opts(g.GRINQH_OPT_GROUPS_PER_WG, force)
+        return g.grinqh_vmm(L.desc, L.pc, L.ps, _dev(torch, x), _dev(torch, lm))
+
+    y = call(0)
+    assert torch.equal(y, call(1)) == mm and torch.equal(y, call(2)) == (not mm)
+    idx = np.unique(np.concatenate([np.arange(0, N, 97), np.arange(N - tile_n, N)]))
+    ref = orc.vmm_batch(np.ascontiguousarray(L.codes[idx]), np.ascontiguousarray(L.scales[:, idx]), x, lm, levels)
+    assert np.abs(_host(y)[:, idx] - ref).max() <= 1e-4 * np.abs(ref).max()
