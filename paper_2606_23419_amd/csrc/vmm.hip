@@ -1,5 +1,6 @@
 // Nested-precision decode VMM (Sec. 3.3 reconstruction with the midpoint
-// bias; App. C.1 sparse bit-loading), first version: correctness first.
+// bias; App. C.1 sparse bit-loading), the plainest form: it runs under
+// GRINQH_KERNEL_GENERAL only, for tests.
 //
 // Grid: (tiles x K-splits, tokens).  A workgroup owns one tile of T outputs
 // and a range of whole groups.  Its 256 threads form lane groups of T/16

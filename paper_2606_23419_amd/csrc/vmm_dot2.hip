@@ -1,5 +1,7 @@
-// Nested-precision decode VMM for 2-bit planes (Sec. 3.3 reconstruction with
-// the midpoint bias; App. C.1 sparse bit-loading), laid out for CDNA4.
+// Nested-precision decode VMM plane by plane (Sec. 3.3 reconstruction with the
+// midpoint bias; App. C.1 sparse bit-loading), laid out for CDNA4.  It runs under
+// GRINQH_KERNEL_PER_PLANE only: the independent kernel that tests hold the default
+// ones against.
 //
 // Work items are plane rows: (channel k, plane j) for j = 1 .. the depth that
 // k's level asks for (for B > 1 tokens, the deepest of the B levels).  A

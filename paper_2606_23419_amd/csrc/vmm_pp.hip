@@ -40,6 +40,8 @@ namespace {
 
 using namespace vmmdev;
 
+constexpr int kSgGroups = 2;                 // groups per workgroup
+
 // 16 outputs, two channels, planes (j, j+1) of each: w?a = plane j, w?b = j+1.
 __device__ __forceinline__ void consume_double(uint32_t w1a, uint32_t w1b, uint32_t w2a,
                                                uint32_t w2b, uint32_t m0, uint32_t xp,
@@ -107,16 +109,17 @@ __device__ __forceinline__ float double_offset_factor(int e) {
   return ((e >> 1) & 1) ? 0.0625f : 1.0f;
 }
 
-template <int LPR, int D, bool TOPK>
+template <int LPR, bool TOPK>
 __global__ __launch_bounds__(256) void k_vmm_sg(
-    const uint16_t* __restrict__ x, const uint8_t* __restrict__ lm, int gw, int groups, int fused,
+    const uint16_t* __restrict__ x, const uint8_t* __restrict__ lm, int groups, int fused,
     const uint8_t* __restrict__ codes, const uint16_t* __restrict__ scales, float* __restrict__ y,
     Layer L, Thresholds th, TopkCuts tk, uint8_t* __restrict__ lm_out) {
   constexpr int T = LPR * 16;            // outputs of the tile
   constexpr int PLANE = T / 4;           // bytes of one plane row
   constexpr int NLG = 64 / LPR;          // lane groups per wave
   constexpr int kWaves = 4;
-  constexpr int MAXG = 2;                // groups per workgroup at most; gw is 1 or 2
+  constexpr int MAXG = kSgGroups;
+  constexpr int D = 4;                   // register sets of the ring of batches
   constexpr int BR = 2 * NLG;            // big rows per batch
   constexpr int SR = 4 * NLG;            // small rows per batch
   constexpr int MB = kGroup / BR + 2;   // batches of one group's list at most
@@ -135,11 +138,11 @@ __global__ __launch_bounds__(256) void k_vmm_sg(
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5, hl = lane & 31;
   const int t = blockIdx.x;
-  const int g0 = blockIdx.y * gw;
-  const int ng = min(gw, groups - g0);
+  const int g0 = blockIdx.y * MAXG;
+  const int ng = min(MAXG, groups - g0);
   // loads first: x and the level map of this lane's row (lanes 0-31 the
   // first group, 32-63 the second).  They need no field of L, so they go
-  // out before the wave waits for the layer's scalars (x, lm, gw, groups and
+  // out before the wave waits for the layer's scalars (x, lm, groups and
   // fused lead the argument list and arrive preloaded in scalar registers)
   const int gg = half;
   const bool valid = gg < ng;
@@ -378,15 +381,15 @@ __global__ __launch_bounds__(256) void k_vmm_sg(
 }
 
 template <int LPR>
-void launch_sg(int gw, hipStream_t s, const void* codes, const void* scales, const void* x,
+void launch_sg(hipStream_t s, const void* codes, const void* scales, const void* x,
                const uint8_t* lm, float* y, const Layer& L, int fused, const Thresholds& th,
                const TopkCuts& tk, uint8_t* lm_out) {
-  const dim3 grid((unsigned)L.tiles, (unsigned)((L.groups + gw - 1) / gw));
+  const dim3 grid((unsigned)L.tiles, (unsigned)((L.groups + kSgGroups - 1) / kSgGroups));
   if (fused == 2)
-    hipLaunchKernelGGL((k_vmm_sg<LPR, 4, true>), grid, dim3(256), 0, s, (const uint16_t*)x, lm, gw, L.groups,
+    hipLaunchKernelGGL((k_vmm_sg<LPR, true>), grid, dim3(256), 0, s, (const uint16_t*)x, lm, L.groups,
                        fused, (const uint8_t*)codes, (const uint16_t*)scales, y, L, th, tk, lm_out);
   else
-    hipLaunchKernelGGL((k_vmm_sg<LPR, 4, false>), grid, dim3(256), 0, s, (const uint16_t*)x, lm, gw, L.groups,
+    hipLaunchKernelGGL((k_vmm_sg<LPR, false>), grid, dim3(256), 0, s, (const uint16_t*)x, lm, L.groups,
                        fused, (const uint8_t*)codes, (const uint16_t*)scales, y, L, th, tk, lm_out);
 }
 
@@ -428,15 +431,14 @@ bool vmm_pp_takes(const Layer& L, int B) {
 int launch_vmm_pp(const Layer& L, const void* codes, const void* scales, const void* x,
                   const uint8_t* level_map, const Thresholds* th, const TopkCuts* tk,
                   uint8_t* level_map_out, float* y, hipStream_t s) {
-  constexpr int gw = 2;   // groups per workgroup
   Thresholds none{};
   TopkCuts nocuts{};
   const Thresholds& tt = th ? *th : none;
   const TopkCuts& cc = tk ? *tk : nocuts;
   const int fused = th ? 1 : (tk ? 2 : 0);   // levels graded here: thresholds, top-k
-  if (L.T == 256) launch_sg<16>(gw, s, codes, scales, x, level_map, y, L, fused, tt, cc, level_map_out);
-  else if (L.T == 512) launch_sg<32>(gw, s, codes, scales, x, level_map, y, L, fused, tt, cc, level_map_out);
-  else launch_sg<64>(gw, s, codes, scales, x, level_map, y, L, fused, tt, cc, level_map_out);
+  if (L.T == 256) launch_sg<16>(s, codes, scales, x, level_map, y, L, fused, tt, cc, level_map_out);
+  else if (L.T == 512) launch_sg<32>(s, codes, scales, x, level_map, y, L, fused, tt, cc, level_map_out);
+  else launch_sg<64>(s, codes, scales, x, level_map, y, L, fused, tt, cc, level_map_out);
   return check_launch("vmm (sorted rows)");
 }
 
