@@ -719,7 +719,8 @@ def test_topk_and_prefill_graph_replays(g, torch, opts):
 @pytest.mark.parametrize("tile_n", [256, 512, 1024])
 def test_vmm_groups_per_workgroup(g, torch, gw, tile_n, kernel, opts):
     # K = 1152 is 9 groups: every gw > 1 leaves a ragged last workgroup.  At
-    # B = 1 the plane-pair kernel runs unless the per-plane kernel is forced.
+    # B = 1 gw = 1 selects the matrix-core kernel and 2..4 the register kernel
+    # (two groups each time) unless the per-plane kernel is forced, which takes gw.
     opts(g.GRINQH_OPT_GROUPS_PER_WG, gw)
     if kernel == "dot2":
         opts(g.GRINQH_OPT_VMM_KERNEL, g.GRINQH_KERNEL_PER_PLANE)
@@ -738,8 +739,9 @@ def test_vmm_groups_per_workgroup(g, torch, gw, tile_n, kernel, opts):
 @pytest.mark.parametrize("tile_n", [256, 512, 1024])
 @pytest.mark.parametrize("levels", [(0, 2, 4, 6, 8), (0, 2, 4, 6), (0, 2, 4)])
 def test_vmm_batch1_depth_classes(g, torch, gw, tile_n, levels, opts):
-    # The batch-1 kernel sorts each wave's rows into those read to 3-4 planes
-    # and those read to 1-2, and pads each class to whole batches: a group
+    # The register kernel (gw = 2) sorts its rows into those read to 3-4 planes
+    # and those read to 1-2, and pads each class to whole batches; the matrix-core
+    # kernel (gw = 1) lists plane rows in blocks of 16: a group
     # with nothing to read, one at full depth, and random depths, for b_max
     # 8, 6 and 4, through the level-map and the fused-threshold entry points.
     # K = 1152 is 9 groups: a ragged last workgroup at gw = 2.
@@ -804,8 +806,7 @@ def test_vmm_entry_points_and_accumulate(g, torch, K, N, tile_n):
                                            ((0, 2, 4, 6, 8), 1024), ((0, 2, 4, 6), 512),
                                            ((0, 2, 3, 4, 8), 512), ((0, 2, 3, 4, 8), 1024)])
 def test_vmm_per_plane_depth_mix(g, torch, gw, levels, tile_n, opts):
-    # The per-plane kernel (batches, 1-bit planes, and 2-bit planes at B = 1
-    # when forced): per-token depths, lone last planes paired across rows
+    # The per-plane kernel (forced): per-token depths, lone last planes paired across rows
     # (odd and even counts of them), ragged workgroups (K = 1152), through
     # the level-map and the fused-threshold entry points.
     opts(g.GRINQH_OPT_GROUPS_PER_WG, gw)
