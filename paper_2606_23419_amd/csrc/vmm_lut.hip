@@ -29,8 +29,9 @@
 // 4096 -> 28672 60.3 / 53.4 / 49.3, 14336 -> 4096 33.6 / 31.1 / 30.5, 1024 -> 1024 11.0 / 6.9 /
 // 6.3.  Where every channel is at 8 bits nothing is left out and the lookups' bank
 // conflicts (random 512-byte tables) bound it: 4096 -> 6144 22.0 / 22.6 / 22.0, 14336 ->
-// 4096 51.9 / 49.1 / 48.6, two tokens of 1536 -> 10240 25.0 / 26.7 / 25.1, of 1024 -> 28672
-// 41.1 / 44.5 / 42.0.
+// 4096 51.9 / 49.1 / 48.6.  Several tokens, without the list / with it, a token's workgroups
+// apart / tokens side by side: two of 1536 -> 10240 at 8 bits 23.5 / 25.8 / 21.9, of 1024 -> 28672
+// 39.0 / 42.3 / 36.3, four of 4096 -> 28672 306 / 305 / 197 and at 4 bits 171 / 174 / 145.
 #include <algorithm>
 #include <type_traits>
 
@@ -71,25 +72,41 @@ __global__ __launch_bounds__(kLutThreads) void k_vmm_lut(const uint8_t* __restri
                                                         const uint16_t* __restrict__ x,
                                                         const uint8_t* __restrict__ lm,
                                                         float* __restrict__ y, Layer L, LutDesc D,
-                                                        int groups_per_split, int splits, int fused,
+                                                        int groups_per_split, int splits, int inner, int B, int fused,
                                                         Thresholds th, uint8_t* __restrict__ lm_out) {
   extern __shared__ __align__(16) uint16_t s_lut[];          // [levels][kSub][2^b]
   __shared__ float s_red[kLutThreads / 64][kSub];
   __shared__ uint32_t s_ent[MINE * kLutThreads];              // active channels: x | row << 16 | level << 27
   __shared__ __align__(16) int s_cnt[kMaxLevels][kLutThreads / 64];         // channels of a level in a wave's share
 
-  // Work order: the K splits of a sub-tile, then the sub-tiles of a tile,
-  // are consecutive work items, and consecutive items run on one XCD
-  // (workgroup id mod 8 picks the XCD): its L2 then serves the sub-tiles'
-  // shared 128-byte plane lines and the splits' shared tables.
-  const int subs = L.T / kSub;
+  // Work order: consecutive work items run on one XCD (workgroup id mod 8 picks
+  // the XCD), so that its L2 serves what they share.  One token: the K splits of
+  // a sub-tile (its tables), then the sub-tiles of a tile (128-byte plane lines).
+  // Several: up to eight tokens, the sub-tiles of a tile, its splits, as the tokens
+  // share every plane line: with a token's workgroups apart from the next's
+  // each token fetched the codes again, 423 MB of 59 for eight tokens of 4096 ->
+  // 28672 at 4 bits of 4, 289 us; now 164.
+  const int sub_bits = __builtin_ctz((unsigned)L.T) - 6, subs = 1 << sub_bits;
+  static_assert(kSub == 64, "sub_bits");
   const int nwg = gridDim.x;
   const int item = (nwg % 8 == 0) ? (int)(blockIdx.x % 8) * (nwg / 8) + (int)(blockIdx.x / 8)
                                   : (int)blockIdx.x;
-  const int tile_sub = item / splits;
-  const int split = item % splits;
-  const int t = tile_sub / subs, sub = tile_sub % subs;
-  const int tok = blockIdx.y;
+  int t, sub, split, tok = 0;
+  if (inner == 1) {
+    const int tile_sub = item / splits;
+    split = item - tile_sub * splits;
+    t = tile_sub >> sub_bits;
+    sub = tile_sub & (subs - 1);
+    tok = blockIdx.y;
+  } else {
+    const int of_tok = item / inner;
+    t = of_tok / (splits << sub_bits);
+    const int in_tile = of_tok - t * (splits << sub_bits);
+    split = in_tile >> sub_bits;
+    sub = in_tile & (subs - 1);
+    tok = (int)blockIdx.y * inner + item - of_tok * inner;
+    if (tok >= B) return;
+  }
   const int n0 = t * L.T + sub * kSub;       // first output of the sub-tile
   const int g0 = split * groups_per_split;
   const int g1 = min(g0 + groups_per_split, L.groups);
@@ -398,25 +415,18 @@ int lut_desc(const Layer& L, LutDesc* D) {
 // 4096 -> 6144 13.8 with g = 4, 16.4 with 8; 4096 -> 4096 10.8 with 4, 13.0 with 8, 14.9
 // with 2; 14336 -> 4096 30.7 with 14 (two workgroups per CU), 33.4 with 16, 35.5 with
 // 8; 1024 -> 1024 6.3 with 1, 8.7 with 4.  More than eight groups only where K is long
-// (4096 -> 28672 49.3 with 8, 51.9 with 16; two tokens 90.7 and 92.8), or with 1-bit
-// planes and more than two columns per CU (two tokens of 4096 -> 28672 139.5 with 8,
-// 132.7 with 16; one token, less than that, 72.1 and 75.4), or where the tables weigh
-// more: with a table of 8 bits (40 KB a copy) and at least 32 (column, group) units per
-// CU, so that up to sixteen groups still leave two workgroups per CU, the longer of
-// equal runs is taken, with 2-bit planes only up to 256 sub-tiles (beyond, 4096 -> 28672, two tokens at
-// 8 bits 146 with 8 and 156 with 16).  Four tokens of 4096 -> 4096 at 8 / 4 bits 39.9 /
-// 27.6 with 8, 34.8 / 24.4 with 16, with 1-bit planes 66.5 / 40.5 and 58.2 / 38.1.
-static int groups_per_workgroup(int groups, int subtiles, int B, int cus, int u, int entries) {
-  const long columns = (long)subtiles * B;
-  const bool heavy = entries >= 256 && columns * groups >= 32l * cus && (u == 1 || subtiles <= 256);
-  const int most = std::min(heavy || (u == 1 && columns > 2 * cus) ? 16 : std::max(8, (groups + 3) / 4),
-                            std::min(groups, kMaxRun / kGroup));
+// (one token of 4096 -> 28672 49.3 with 8, 51.9 with 16), for several tokens too: they
+// share tables and plane lines through L2, so longer runs don't save them (four of
+// 4096 -> 4096 at 8 bits 33.5 with 8, 37.0 with 16; eight of 14336 -> 4096 at 4 bits of 4
+// 88 with 8, 105 with 16).
+static int groups_per_workgroup(int groups, long columns, int cus) {
+  const int most = std::min(std::max(8, (groups + 3) / 4), std::min(groups, kMaxRun / kGroup));
   int best = 1;
   long best_cost = 0;
   for (int g = 1; g <= most; ++g) {
     const long splits = (groups + g - 1) / g;
     const long cost = (columns * splits + cus - 1) / cus * (g + 4) + g;
-    if (g == 1 || cost < best_cost || (heavy && cost == best_cost)) {
+    if (g == 1 || cost < best_cost) {
       best = g;
       best_cost = cost;
     }
@@ -437,17 +447,18 @@ int launch_vmm_lut(const Layer& L, const void* codes, const void* luts, const vo
     hipLaunchKernelGGL(k_zero_lut, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, y, n);
   }
   const long subtiles = (long)L.tiles * (L.T / kSub);
-  int gps = groups_per_workgroup(L.groups, (int)subtiles, B, device_cus(), L.u, D.entries);
+  int gps = groups_per_workgroup(L.groups, subtiles * B, device_cus());
   if (const int v = option(&Options::lut_groups)) gps = v <= L.groups ? v : L.groups;
   gps = gps > kMaxRun / kGroup ? kMaxRun / kGroup : gps;
   const long splits = (L.groups + gps - 1) / gps;
-  const dim3 grid((unsigned)(subtiles * splits), (unsigned)B);
+  const int rows = (B + 7) / 8, inner = (B + rows - 1) / rows;   // tokens side by side: up to 8
+  const dim3 grid((unsigned)(subtiles * splits * inner), (unsigned)rows);
   Thresholds none{};
   const Thresholds& tt = th ? *th : none;
   const int fused = th != nullptr;
 #define GRINQH_LUT(UU, MM)                                                                                    \
   hipLaunchKernelGGL((k_vmm_lut<UU, MM>), grid, dim3(kLutThreads), lds, s, (const uint8_t*)codes,              \
-                     (const uint16_t*)luts, (const uint16_t*)x, level_map, y, L, D, gps, (int)splits, fused, \
+                     (const uint16_t*)luts, (const uint16_t*)x, level_map, y, L, D, gps, (int)splits, inner, B, fused, \
                      tt, level_map_out)
   const int run = gps * kGroup;
   if (L.u == 2) {

@@ -41,3 +41,28 @@ def test_lut_list_edges(g, torch, opts, K, levels, tile_n, gps):  # noqa: F811
         top = max(np.abs(t.astype(np.float64)).max() for t in L.tables.values())
         bound = (K + 8) * 2.0 ** -24 * top * np.abs(x.astype(np.float64)).sum(axis=1, keepdims=True)
         assert np.all(np.abs(y - ref) <= bound), (runs, np.max(np.abs(y - ref) / np.maximum(bound, 1e-30)))
+
+
+@pytest.mark.parametrize("B", [2, 3, 7, 8, 9, 11, 16, 17, 33])
+@pytest.mark.parametrize("K,N,levels,tile_n,gps", [
+    (640, 1536, (0, 2, 4, 8), 512, 2), (384, 1024, (0, 2, 4, 6, 8), 1024, 1), (256, 768, (0, 2, 4), 256, 16),
+    (384, 1536, (0, 2, 3, 4, 8), 512, 2), (512, 2048, (0, 2, 4), 2048, 3)])
+def test_lut_tokens_side_by_side(g, torch, opts, K, N, levels, tile_n, gps, B):  # noqa: F811
+    # up to eight tokens share a row of workgroups; where the tokens don't fill the
+    # last row its spare workgroups leave.  Every token, tile, sub-tile and split, and the
+    # level map that the first sub-tile's workgroups write
+    opts(g.GRINQH_OPT_LUT_GROUPS, str(gps))
+    L = LutLayer(g, torch, K, N, levels, layer=K + N, tile_n=tile_n)
+    x = inputs.activations_t3(K, B, 98)
+    th = np.quantile(np.abs(x.astype(np.float64)), np.linspace(0.2, 0.8, len(levels) - 1)).astype(np.float32)
+    lm = (np.abs(x.astype(np.float32))[:, :, None] >= th).sum(axis=2).astype(np.uint8)
+    ref = L.ref(x, lm)
+    top = max(np.abs(t.astype(np.float64)).max() for t in L.tables.values())
+    bound = (K + 8) * 2.0 ** -24 * top * np.abs(x.astype(np.float64)).sum(axis=1, keepdims=True)
+    y = L.run(g, torch, x, lm)
+    assert np.all(np.abs(y - ref) <= bound)
+    lo = torch.full((B, K), 255, dtype=torch.uint8, device="cuda")
+    buf = torch.full((B + 1, N), 7.0, device="cuda")
+    g.grinqh_vmm_lut_threshold(L.desc, L.pc, L.luts, _dev(torch, x), th, y=buf[:B], level_map_out=lo)
+    assert np.all(np.abs(_host(buf)[:B] - ref) <= bound) and bool((buf[B:] == 7.0).all())
+    assert np.array_equal(_host(lo), lm)
