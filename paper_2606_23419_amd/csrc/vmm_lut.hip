@@ -417,8 +417,7 @@ int lut_desc(const Layer& L, LutDesc* D) {
 // 8; 1024 -> 1024 6.3 with 1, 8.7 with 4.  More than eight groups only where K is long
 // (one token of 4096 -> 28672 49.3 with 8, 51.9 with 16), for several tokens too: they
 // share tables and plane lines through L2, so longer runs don't save them (four of
-// 4096 -> 4096 at 8 bits 33.5 with 8, 37.0 with 16; eight of 14336 -> 4096 at 4 bits of 4
-// 88 with 8, 105 with 16).
+// 4096 -> 4096 at 8 bits 33.5 with 8, 37.0 with 16).
 static int groups_per_workgroup(int groups, long columns, int cus) {
   const int most = std::min(std::max(8, (groups + 3) / 4), std::min(groups, kMaxRun / kGroup));
   int best = 1;
